@@ -65,6 +65,18 @@ def test_ga_matches_oracle(orc, P, L, k, elite, seed, gen):
     _check(G, out, dec, ref, rdec)
 
 
+@pytest.mark.parametrize("L", [255, 256, 1793, 2047, 2048, 2049, 2560, 2561, 4097, 18433])
+def test_ga_chunk_edges(orc, L):
+    """Genome lengths around the 256-gene mask blocks and the workgroups' chunk
+    of at most 2048 genes, every gene mutating in half of the runs."""
+    P = 9
+    g = np.random.default_rng(L)
+    G = g.normal(size=(P, L)).astype(np.float32)
+    fit = g.normal(size=P).astype(np.float32)
+    out, dec, ref, rdec = _run_both(orc, fit, G, seed=L, generation=2, p_mut=1.0 if L % 2 else 0.1, p_cross=0.7)
+    _check(G, out, dec, ref, rdec)
+
+
 def test_ga_workload_size_decisions(orc):
     """1024 genomes of 8710 genes (the uneven-batch population)."""
     P, L = 1024, inputs.GENOME_LEN
