@@ -10,68 +10,137 @@ namespace sr {
 
 namespace {
 
-constexpr int QB = 256;  // voxels (threads) per workgroup
+constexpr int QB = 512;  // threads per workgroup: 8 waves, each 16 voxels (a tile) at a time
 constexpr int OFF_W1 = 0, OFF_B1 = 4096, OFF_W2 = 4160, OFF_B2 = 8256, OFF_W3 = 8320, OFF_B3 = 8704;
 
-// FP32 form: one voxel per thread, the robot's weights staged in LDS and read
-// as broadcasts (every lane reads the same weight).
-__global__ __launch_bounds__(QB) __attribute__((amdgpu_waves_per_eu(1, 2))) void k_query_fp32(const RobotInfo *robots, const float *genomes, const float *B,
-                                                   uint8_t *cls, float *w) {
-    __shared__ float Ws[SR_GENOME_LEN];
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// ---------------------------------------------------------------- FP32 MFMA form
+// Activations are kept transposed (features x voxels), one wave handles 16
+// voxels, and each layer is D = W H^T on v_mfma_f32_16x16x4_f32: lane l of A
+// holds row l%16 and k = l/16, lane l of B column l%16 and k = l/16, lane l of
+// D column l%16 and rows 4(l/16)..+3.  The instruction accumulates its four
+// products as FMAs in ascending k on top of C (measured against an fmaf chain:
+// no mismatch in 2 million results, zeros and denormals among them), so with
+// the bias as the first C and K-steps in ascending order the sums are those of
+// the scalar loop a = b_i; a = fma(W_ij, h_j, a), bit for bit.
+// D row 4 kq + i of output block m is given weight row 16 m + 4 i + kq: then
+// register i of lane quarter kq holds feature 4 (4 m + i) + kq, which is the B
+// operand of K-step 4 m + i of the next layer, and activations never leave
+// registers.
+// The fragments of K-steps 4 c .. 4 c + 3 of a lane are one 16-byte LDS read.
+// Bound by the tanh and sin/cos of every feature (about 1400 VALU instructions
+// a tile of 16 voxels) beside 144 matrix instructions of 32 cycles, which the
+// other waves of the SIMD overlap: four waves a SIMD, so the fragments are
+// read from LDS for every tile instead of held in registers (with them in
+// registers, two waves a SIMD, 1.23 ms instead of 1.07 at 4096 robots of 10^3).
+// Measured against one voxel per thread with weights broadcast from LDS, which
+// the LDS reads bound: 4096 robots of 10^3 2.26 -> 1.07 ms (66 TFLOP/s of the
+// MLP's products), 30 robots of 5^3 63 -> 14 us.
+constexpr int FRAG3 = 2 * 4 * 4 * 64;  // first fragment quad of the output layer
+constexpr int NFRAG = FRAG3 + 4 * 64;
+
+__global__ __launch_bounds__(QB) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_query_fp32(
+    const RobotInfo *robots, const float *genomes, const float *B, uint8_t *cls, float *w, int tiles) {
+    __shared__ float4 Ws[NFRAG];  // [layer][m][c][lane], then [c][lane] of the output layer
+    __shared__ float bias[64 + 64 + 16];
     __shared__ float Bs[3 * SR_PE_M];
     const int r = blockIdx.y;
     const RobotInfo ri = robots[r];
-    const int nv = ri.n * ri.n * ri.n;
-    if ((int)(blockIdx.x * QB) >= nv) return;
+    const int n = ri.n, nv = n * n * n;
+    if ((int)(blockIdx.x * tiles * 16) >= nv) return;
     const float *g = genomes + (size_t)r * SR_GENOME_LEN;
-    for (int q = threadIdx.x; q < SR_GENOME_LEN; q += QB) Ws[q] = g[q];
-    for (int q = threadIdx.x; q < 3 * SR_PE_M; q += QB) Bs[q] = B[q];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int col = lane & 15, kq = lane >> 4;  // voxel column and k of this lane
+    {
+        float *Wf = reinterpret_cast<float *>(Ws);
+        for (int q = tid; q < 64 * 64; q += QB) {
+            const int row = q >> 6, j = q & 63;
+            // row 16 m + 4 i + kq' is A row 4 kq' + i of block m; feature j is k = j % 4 of K-step j / 4
+            const int at = ((row >> 4) * 4 + (j >> 4)) * 64 + (j & 3) * 16 + 4 * (row & 3) + ((row >> 2) & 3);
+            Wf[4 * at + ((j >> 2) & 3)] = g[OFF_W1 + q];
+            Wf[4 * (at + 4 * 4 * 64) + ((j >> 2) & 3)] = g[OFF_W2 + q];
+        }
+        for (int q = tid; q < 16 * 64; q += QB) {
+            const int row = q >> 6, j = q & 63;  // rows in their own order
+            Wf[4 * (FRAG3 + (j >> 4) * 64 + (j & 3) * 16 + row) + ((j >> 2) & 3)] = q < 6 * 64 ? g[OFF_W3 + q] : 0.f;
+        }
+        for (int q = tid; q < 64; q += QB) {
+            bias[q] = g[OFF_B1 + q];
+            bias[64 + q] = g[OFF_B2 + q];
+        }
+        if (tid < 16) bias[128 + tid] = tid < 6 ? g[OFF_B3 + tid] : 0.f;
+        for (int q = tid; q < 3 * SR_PE_M; q += QB) Bs[q] = B[q];
+    }
     __syncthreads();
-    const int vid = blockIdx.x * QB + threadIdx.x;
-    if (vid >= nv) return;
-    const int n = ri.n;
+
     const float inv = 1.0f / (float)n;
-    const float vx = ((vid % n) + 0.5f) * inv, vy = (((vid / n) % n) + 0.5f) * inv, vz = ((vid / (n * n)) + 0.5f) * inv;
-    float gam[2 * SR_PE_M];
+    const int vend = min(nv, (int)(blockIdx.x + 1) * tiles * 16);
+    for (int v0 = (blockIdx.x * tiles + (tid >> 6)) * 16; v0 < vend; v0 += QB / 4) {
+        const int vid = v0 + col;
+        const int vc = vid < nv ? vid : nv - 1;
+        const float vx = ((vc % n) + 0.5f) * inv, vy = (((vc / n) % n) + 0.5f) * inv, vz = ((vc / (n * n)) + 0.5f) * inv;
+        // the tile loop must not hoist the fragments and biases into registers
+        int at = lane, bq = kq;
+        __asm__ volatile("" : "+v"(at), "+v"(bq));
+        float h[16];
 #pragma unroll
-    for (int q = 0; q < SR_PE_M; ++q) {
-        // 2 pi (B v) taken as pi * (2 B v) so the angle scaling is exact
-        const float t = 2.0f * fmaf(Bs[3 * q + 2], vz, fmaf(Bs[3 * q + 1], vy, Bs[3 * q] * vx));
-        float s, c;
-        sincospif(t, &s, &c);
-        gam[q] = c;
-        gam[SR_PE_M + q] = s;
+        for (int b = 0; b < 8; ++b) {
+            // 2 pi (B v) taken as pi * (2 B v) so the angle scaling is exact
+            const int q = 4 * b + bq;
+            const float t = 2.0f * fmaf(Bs[3 * q + 2], vz, fmaf(Bs[3 * q + 1], vy, Bs[3 * q] * vx));
+            sincospif(t, &h[8 + b], &h[b]);
+        }
+#pragma unroll
+        for (int layer = 0; layer < 2; ++layer) {
+            f32x4 acc[4];
+#pragma unroll
+            for (int m = 0; m < 4; ++m)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) acc[m][i] = bias[64 * layer + 16 * m + 4 * i + bq];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                float4 f[4];
+#pragma unroll
+                for (int m = 0; m < 4; ++m) f[m] = Ws[((layer * 4 + m) * 4 + c) * 64 + at];
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int m = 0; m < 4; ++m) {
+                        const float a = e == 0 ? f[m].x : e == 1 ? f[m].y : e == 2 ? f[m].z : f[m].w;
+                        acc[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, h[4 * c + e], acc[m], 0, 0, 0);
+                    }
+            }
+#pragma unroll
+            for (int m = 0; m < 4; ++m)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) h[4 * m + i] = tanhf(acc[m][i]);
+        }
+        // output layer: rows 0..5 of a 16-row block, in their own order
+        f32x4 acc;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[i] = bias[128 + 4 * bq + i];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const float4 f = Ws[FRAG3 + c * 64 + at];
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(f.x, h[4 * c], acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(f.y, h[4 * c + 1], acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(f.z, h[4 * c + 2], acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(f.w, h[4 * c + 3], acc, 0, 0, 0);
+        }
+        // lane col (kq = 0) holds o0..o3, lane col + 16 (kq = 1) holds o4, o5
+        const float o4 = __shfl(acc[0], col + 16, 64);
+        const float o5 = __shfl(acc[1], col + 16, 64);
+        if (kq == 0 && vid < nv) {
+            const float o[5] = {acc[0], acc[1], acc[2], acc[3], o4};
+            int best = 0;
+#pragma unroll
+            for (int q = 1; q < 5; ++q)
+                if (o[q] > o[best]) best = q;
+            cls[ri.vox_base + vid] = (uint8_t)best;
+            w[ri.vox_base + vid] = 1.0f / (1.0f + expf(-o5));
+        }
     }
-    float h1[64];
-#pragma unroll
-    for (int i = 0; i < 64; ++i) {
-        float a = Ws[OFF_B1 + i];
-#pragma unroll
-        for (int j = 0; j < 64; ++j) a = fmaf(Ws[OFF_W1 + 64 * i + j], gam[j], a);
-        h1[i] = tanhf(a);
-    }
-    float h2[64];
-#pragma unroll
-    for (int i = 0; i < 64; ++i) {
-        float a = Ws[OFF_B2 + i];
-#pragma unroll
-        for (int j = 0; j < 64; ++j) a = fmaf(Ws[OFF_W2 + 64 * i + j], h1[j], a);
-        h2[i] = tanhf(a);
-    }
-    float o[6];
-#pragma unroll
-    for (int i = 0; i < 6; ++i) {
-        float a = Ws[OFF_B3 + i];
-#pragma unroll
-        for (int j = 0; j < 64; ++j) a = fmaf(Ws[OFF_W3 + 64 * i + j], h2[j], a);
-        o[i] = a;
-    }
-    int best = 0;
-#pragma unroll
-    for (int q = 1; q < 5; ++q)
-        if (o[q] > o[best]) best = q;
-    cls[ri.vox_base + vid] = (uint8_t)best;
-    w[ri.vox_base + vid] = 1.0f / (1.0f + expf(-o[5]));
 }
 
 // ---------------------------------------------------------------- BF16 MFMA form
@@ -90,7 +159,6 @@ __global__ __launch_bounds__(QB) __attribute__((amdgpu_waves_per_eu(1, 2))) void
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int WROW = 72;  // padded LDS row of a BF16 weight matrix
 
 __device__ __forceinline__ unsigned short f2bf(float f) {
@@ -215,9 +283,14 @@ hipError_t launch_query(const RobotInfo *robots, int R, int max_side, const floa
         hipLaunchKernelGGL(k_query_bf16, dim3(R), dim3(256), 0, st, robots, genomes, B, cls, w);
         return hipGetLastError();
     }
-    const int maxv = max_side * max_side * max_side;
-    dim3 grid((maxv + QB - 1) / QB, R);
-    hipLaunchKernelGGL(k_query_fp32, grid, dim3(QB), 0, st, robots, genomes, B, cls, w);
+    // tiles of 16 voxels per workgroup: a multiple of its 8 waves, as many as
+    // still leave two workgroups for each of 256 CUs, so that the weights' way
+    // into LDS is shared by many tiles
+    const int maxt = (max_side * max_side * max_side + 15) / 16;
+    const int64_t want = (int64_t)R * maxt / (512 * 8);
+    const int tiles = 8 * (int)(want < 1 ? 1 : want > 16 ? 16 : want);
+    hipLaunchKernelGGL(k_query_fp32, dim3((maxt + tiles - 1) / tiles, R), dim3(QB), 0, st, robots, genomes, B, cls, w,
+                       tiles);
     return hipGetLastError();
 }
 

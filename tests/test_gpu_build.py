@@ -60,6 +60,20 @@ def test_query_matches_oracle(orc, prec, margin, wtol):
     assert agree / total > (0.9999 if prec == SR_QUERY_FP32 else 0.98)
 
 
+@pytest.mark.parametrize("prec", [SR_QUERY_FP32, SR_QUERY_BF16])
+@pytest.mark.parametrize("copies", [40, 300])
+def test_query_split_does_not_change_bits(prec, copies):
+    """How many voxels a workgroup takes depends on the population: the same
+    robots alone and among many must give the same bits."""
+    few = [12, 5, 9, 1, 10]
+    B = inputs.gaussian_B()
+    G = inputs.random_genomes(len(few), seed=47)
+    P, cls, w = _gpu_query(few, G, B, prec)
+    Q, many_cls, many_w = _gpu_query(few * copies, np.tile(G, (copies, 1)), B, prec)
+    assert np.array_equal(many_cls, np.tile(cls, copies))
+    assert np.array_equal(many_w.view(np.uint32), np.tile(w, copies).view(np.uint32))
+
+
 def test_bf16_and_fp32_builds_are_close():
     sides = [10] * 64
     B = inputs.gaussian_B()
