@@ -708,21 +708,14 @@ __global__ void k_adj_init(const RobotInfo *robots, int total_slots, const int32
 }
 
 // Per spring: dJ/dk, dJ/da, dJ/dphi in canonical order, from the stencil sums.
-__global__ void k_adj_springs(const RobotInfo *robots, int total_slots, const int32_t *slot_robot, const int32_t *sid,
-                              const int64_t *spring_off, Planes pl, float voxel_len, const float *gk, const float *gs,
-                              const float *gc, float *g_k, float *g_a, float *g_phi) {
-    const int g = blockIdx.x * blockDim.x + threadIdx.x;
-    if (g >= total_slots) return;
-    const int r = slot_robot[g];
-    const RobotInfo ri = robots[r];
-    const int s = g - ri.slot_base;
-    for (int d = 0; d < NDIR; ++d) {
-        const int pi = NDIR * ri.slot_base + d * ri.slots + s;
-        const int id = sid[pi];
-        if (id < 0) continue;
-        const int64_t o = spring_off[r] + id;
+__global__ __launch_bounds__(EACH_SLOTS) void k_adj_springs(const RobotInfo *robots, int total_slots,
+                                                            const int32_t *slot_robot, SpringIndex ix,
+                                                            const int64_t *spring_off, Planes pl, float voxel_len,
+                                                            const float *gk, const float *gs, const float *gc,
+                                                            float *g_k, float *g_a, float *g_phi) {
+    each_spring(robots, total_slots, slot_robot, ix, spring_off, [&](int64_t o, int, int d, int pi, int) {
         const float L0 = voxel_len * sqrtf((float)dir_len2(d));
-        const float kL0 = pl.kL0[pi], kal = pl.kal[pi], kbe = pl.kbe[pi];
+        const float kL0 = pl.k[pi] * L0, kal = pl.kal[pi], kbe = pl.kbe[pi];
         float a = 0.f, cph = 1.f, sph = 0.f;
         if (kL0 != 0.f) {
             if (kbe == 0.f) a = kal / kL0;
@@ -736,7 +729,7 @@ __global__ void k_adj_springs(const RobotInfo *robots, int total_slots, const in
         if (g_k) g_k[o] = gk[pi];
         if (g_a) g_a[o] = L0 * (gs[pi] * cph + gc[pi] * sph);
         if (g_phi) g_phi[o] = L0 * a * (gc[pi] * cph - gs[pi] * sph);
-    }
+    });
 }
 
 // dJ/dw per voxel through the parallel-sum rule.  Write Z = k a e^{i phi} for a
@@ -1105,11 +1098,12 @@ hipError_t launch_adj_init(const RobotInfo *robots, int total_slots, const int32
     return hipGetLastError();
 }
 
-hipError_t launch_adj_springs(const RobotInfo *robots, int total_slots, const int32_t *slot_robot, const int32_t *sid,
+hipError_t launch_adj_springs(const RobotInfo *robots, int total_slots, const int32_t *slot_robot, SpringIndex ix,
                               const int64_t *spring_off, Planes pl, float voxel_len, const float *gk, const float *gs,
                               const float *gc, float *g_k, float *g_a, float *g_phi, hipStream_t st) {
-    hipLaunchKernelGGL(k_adj_springs, dim3((total_slots + 255) / 256), dim3(256), 0, st, robots, total_slots,
-                       slot_robot, sid, spring_off, pl, voxel_len, gk, gs, gc, g_k, g_a, g_phi);
+    if (!g_k && !g_a && !g_phi) return hipSuccess;
+    hipLaunchKernelGGL(k_adj_springs, dim3((total_slots + EACH_SLOTS - 1) / EACH_SLOTS), dim3(EACH_SLOTS), 0, st,
+                       robots, total_slots, slot_robot, ix, spring_off, pl, voxel_len, gk, gs, gc, g_k, g_a, g_phi);
     return hipGetLastError();
 }
 

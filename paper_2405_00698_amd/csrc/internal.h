@@ -59,31 +59,29 @@ struct RobotInfo {
     int32_t pad;
 };
 
-// Spring parameters live in four stencil planes, each [13][slots] per robot
+// Spring parameters live in stencil planes, each [13][slots] per robot
 // (plane index 13 * slot_base + d * slots + lower_slot):
 //   k     stiffness (0 where no spring)
-//   kL0   k * L0
 //   kal   k * L0 * a cos(phi)   (coefficient of sin(w t) in k L(t))
-//   kbe   k * L0 * a sin(phi)   (coefficient of cos(w t))
-// so that k L(t) = kL0 + kal sin(w t) + kbe cos(w t); and
-//   kd    dashpot coefficient c beside the spring (Table II model; 0 otherwise).
+//   kbe   k * L0 * a sin(phi)   (coefficient of cos(w t); zero without phases)
+// so that k L(t) = k L0 + kal sin(w t) + kbe cos(w t); and
+//   kd    dashpot coefficient c beside the spring (zero without dashpots; null when the
+//         ground has no damper either)
 struct Planes {
-    float *k, *kL0, *kal, *kbe, *kd;
+    float *k, *kal, *kbe, *kd;
     // per slot: the parallel-sum terms (k_c w, k_c w a cos, k_c w a sin, dashpot)
     // of the voxel whose lowest corner is the slot; the planes above are the
     // explicitly rounded sums of these over each spring's voxels
     float4 *vkp;
 };
 
-// Node incidence for the per-step kernel: for node i of a robot (slot-space
-// index slot_base + i), its global slot and the ranges of its forward
-// (lower endpoint) and backward (upper endpoint) entries.
-struct NodeRow {
-    int32_t gslot, start, mid, end;
-};
-struct Entry {
-    int32_t nbr;   // global slot of the other endpoint
-    int32_t plane; // global plane index of the spring
+// Which springs exist, per slot: bit d of mask is the forward spring of
+// direction d, and base the canonical id (within the robot) of the slot's
+// first forward spring, so spring (slot, d) has id
+// base + popcount(mask & ((1 << d) - 1)).
+struct SpringIndex {
+    int32_t *base;
+    uint16_t *mask;
 };
 
 struct SimConst {
@@ -99,11 +97,13 @@ struct SimConst {
 SimConst make_sim_const(const sr_sim_params &p);
 
 // ---- kernels (launchers); each returns hipError_t of the launch ----
-hipError_t launch_build_mesh(const RobotInfo *robots, int R, int max_side, const sr_sim_params &p,
-                             const uint8_t *cls, const float *w, uint8_t *kept, Planes pl,
-                             int32_t *sid, float4 *x0, float4 *x, float4 *v, int32_t *slot_node,
-                             int32_t *node_slot, NodeRow *rows, Entry *entries, uint8_t *bad_class,
+hipError_t launch_build_mesh(const RobotInfo *robots, int R, int max_side, bool full, const sr_sim_params &p,
+                             const uint8_t *cls, const float *w, uint8_t *kept, Planes pl, SpringIndex ix,
+                             float4 *x0, float4 *x, float4 *v, int32_t *slot_node, uint8_t *bad_class,
                              uint8_t *diverged, hipStream_t st);
+// host: pinned int64 [2 R + 3] = first bad robot or -1, node offsets, spring offsets
+hipError_t launch_finish_build(const RobotInfo *robots, int R, uint8_t *bad_class, int64_t *mass_off,
+                               int64_t *spring_off, int64_t *step, int64_t *host, hipStream_t st);
 
 hipError_t launch_query(const RobotInfo *robots, int R, int max_side, const float *genomes, const float *B,
                         int precision, uint8_t *cls, float *w, hipStream_t st);
@@ -137,7 +137,7 @@ hipError_t launch_adjoint(int n, bool phase, const RobotInfo *robots, const int3
 hipError_t launch_adj_init(const RobotInfo *robots, int total_slots, const int32_t *slot_robot, const float4 *x0,
                            const float *dJ, float4 *lx, float4 *lv, float *gk, float *gs, float *gc, float *gd,
                            hipStream_t st);
-hipError_t launch_adj_springs(const RobotInfo *robots, int total_slots, const int32_t *slot_robot, const int32_t *sid,
+hipError_t launch_adj_springs(const RobotInfo *robots, int total_slots, const int32_t *slot_robot, SpringIndex ix,
                               const int64_t *spring_off, Planes pl, float voxel_len, const float *gk, const float *gs,
                               const float *gc, float *g_k, float *g_a, float *g_phi, hipStream_t st);
 hipError_t launch_adj_genome(const RobotInfo *robots, int R, int total_vox, const int32_t *vox_robot,
@@ -146,10 +146,13 @@ hipError_t launch_adj_genome(const RobotInfo *robots, int R, int total_vox, cons
                              const float *B, float *dJdw, float *g_gen, hipStream_t st);
 hipError_t launch_advance(int64_t *d_step, int n, hipStream_t st);
 
-hipError_t launch_plain_step(const RobotInfo *robots, int R, int total_slots, const NodeRow *rows,
-                             const Entry *entries, Planes pl, const float4 *x, const float4 *v,
-                             float4 *xn, float4 *vn, const float2 *sc, int t, bool phase,
+hipError_t launch_plain_step(const RobotInfo *robots, int total_slots, SpringIndex ix, Planes pl, const float4 *x,
+                             const float4 *v, float4 *xn, float4 *vn, const float2 *sc, int t, bool phase,
                              const uint8_t *diverged, const int32_t *slot_robot, SimConst c, hipStream_t st);
+
+// x = x0, v = 0, no divergence flag, step 0
+hipError_t launch_reset(int total_slots, int R, const float4 *x0, float4 *x, float4 *v, uint8_t *diverged,
+                        int64_t *step, hipStream_t st);
 
 hipError_t launch_check_div(const RobotInfo *robots, int R, const float4 *x, const float4 *v,
                             uint8_t *diverged, float lim, hipStream_t st);
@@ -177,7 +180,7 @@ hipError_t launch_gather_state(const RobotInfo *robots, int R, int total_slots, 
                                const float4 *v, float *xo, float *vo, int scatter, hipStream_t st);
 
 hipError_t launch_springs_io(const RobotInfo *robots, int R, int total_slots, const int32_t *slot_robot,
-                             const int32_t *slot_node, const int32_t *sid, const int64_t *spring_off,
+                             const int32_t *slot_node, SpringIndex ix, const int64_t *spring_off,
                              Planes pl, float voxel_len, int32_t *ij, float *L0, float *k, float *a,
                              float *phi, const float *k_in, const float *a_in, const float *phi_in,
                              int write, hipStream_t st);

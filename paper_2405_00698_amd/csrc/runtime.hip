@@ -85,12 +85,10 @@ struct sr_pop {
     uint8_t *kept = nullptr;
     float *w = nullptr;
     Planes pl{};
-    int32_t *sid = nullptr;
+    SpringIndex ix{};
     float4 *x0 = nullptr, *xbuf[2] = {nullptr, nullptr}, *vbuf[2] = {nullptr, nullptr};
     int cur = 0;
-    int32_t *slot_node = nullptr, *node_slot = nullptr, *slot_robot = nullptr;
-    NodeRow *rows = nullptr;
-    Entry *entries = nullptr;
+    int32_t *slot_node = nullptr, *slot_robot = nullptr;
     uint8_t *bad_class = nullptr, *diverged = nullptr;
     int64_t *d_step = nullptr;
     int64_t h_step = 0, h_step_stage = 0;
@@ -102,8 +100,9 @@ struct sr_pop {
     // (0: the population's stream, k > 0: side[k - 1])
     std::vector<int> order, lane;
     int64_t *d_mass_off = nullptr, *d_spring_off = nullptr;
-    std::vector<int64_t> h_mass_off, h_spring_off;
-    bool counts_valid = false;
+    // pinned: first bad robot or -1, node offsets [R + 1], spring offsets [R + 1],
+    // written by every build's last kernel
+    int64_t *h_built = nullptr;
     bool built = false;
     bool phase = false;
     bool dash = false;  // spring dashpots: only the +16 persistent kernels
@@ -112,7 +111,6 @@ struct sr_pop {
     int sticky = 0;
     // genome query scratch
     uint8_t *q_cls = nullptr;
-    float *q_w = nullptr;
     int32_t *vox_robot = nullptr;
     // adjoint: checkpoints of (x, v) at steps 0, K, 2K, ... since the build
     int ck_every = 0, ck_cap = 0;
@@ -178,11 +176,11 @@ void pop_free(sr_pop *pop) {
     for (auto s : pop->side) (void)hipStreamDestroy(s);
     for (auto e : pop->ev) (void)hipEventDestroy(e);
     if (pop->cap) (void)hipStreamDestroy(pop->cap);
-    void *ptrs[] = {pop->d_robots, pop->kept, pop->w, pop->pl.k, pop->pl.kL0, pop->pl.kal, pop->pl.kbe, pop->pl.kd, pop->pl.vkp,
-                    pop->sid, pop->x0, pop->xbuf[0], pop->xbuf[1], pop->vbuf[0], pop->vbuf[1],
-                    pop->slot_node, pop->node_slot, pop->slot_robot, pop->rows, pop->entries,
+    void *ptrs[] = {pop->d_robots, pop->kept, pop->w, pop->pl.k, pop->pl.kal, pop->pl.kbe, pop->pl.kd, pop->pl.vkp,
+                    pop->ix.base, pop->ix.mask, pop->x0, pop->xbuf[0], pop->xbuf[1], pop->vbuf[0], pop->vbuf[1],
+                    pop->slot_node, pop->slot_robot,
                     pop->bad_class, pop->diverged, pop->d_step, pop->sc, pop->d_lists, pop->d_mass_off,
-                    pop->d_spring_off, pop->q_cls, pop->q_w, pop->vox_robot, pop->ck_x, pop->ck_v,
+                    pop->d_spring_off, pop->q_cls, pop->vox_robot, pop->ck_x, pop->ck_v,
                     pop->lx, pop->lv, pop->gk, pop->gs, pop->gc, pop->gd, pop->dJdw};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
@@ -192,31 +190,16 @@ void pop_free(sr_pop *pop) {
         for (void *p : seg)
             if (p) (void)hipFree(p);
     }
+    if (pop->h_built) (void)hipHostFree(pop->h_built);
     for (auto e : pop->adj_ev)
         if (e) (void)hipEventDestroy(e);
     if (pop->adj_st) (void)hipStreamDestroy(pop->adj_st);
     if (pop->adj_gst) (void)hipStreamDestroy(pop->adj_gst);
 }
 
-int ensure_counts(sr_pop *pop) {
-    if (pop->counts_valid) return SR_OK;
-    HIPC(pop, hipMemcpyAsync(pop->h_robots.data(), pop->d_robots, sizeof(RobotInfo) * pop->R, hipMemcpyDeviceToHost,
-                             pop->st));
-    HIPC(pop, hipStreamSynchronize(pop->st));
-    pop->h_mass_off.assign(pop->R + 1, 0);
-    pop->h_spring_off.assign(pop->R + 1, 0);
-    for (int r = 0; r < pop->R; ++r) {
-        pop->h_mass_off[r + 1] = pop->h_mass_off[r] + pop->h_robots[r].M;
-        pop->h_spring_off[r + 1] = pop->h_spring_off[r] + pop->h_robots[r].S;
-    }
-    HIPC(pop, hipMemcpyAsync(pop->d_mass_off, pop->h_mass_off.data(), sizeof(int64_t) * (pop->R + 1),
-                             hipMemcpyHostToDevice, pop->st));
-    HIPC(pop, hipMemcpyAsync(pop->d_spring_off, pop->h_spring_off.data(), sizeof(int64_t) * (pop->R + 1),
-                             hipMemcpyHostToDevice, pop->st));
-    HIPC(pop, hipStreamSynchronize(pop->st));
-    pop->counts_valid = true;
-    return SR_OK;
-}
+// node and spring offsets of the last build, host copies
+const int64_t *mass_off(const sr_pop *pop) { return pop->h_built + 1; }
+const int64_t *spring_off(const sr_pop *pop) { return pop->h_built + 2 + pop->R; }
 
 int ensure_sc(sr_pop *pop, int n) {
     if (n <= pop->sc_cap) return SR_OK;
@@ -230,28 +213,17 @@ int ensure_sc(sr_pop *pop, int n) {
     return SR_OK;
 }
 
-// Runs after any build: resets step, buffers and cached counts.
+// Runs after any build: resets the step, forms the node and spring offsets and
+// synchronises, so that a bad class is reported and the counts are on the host.
 int finish_build(sr_pop *pop) {
     pop->cur = 0;
-    HIPC(pop, hipMemcpyAsync(pop->xbuf[1], pop->xbuf[0], sizeof(float4) * pop->total_slots, hipMemcpyDeviceToDevice,
-                             pop->st));
-    HIPC(pop, hipMemcpyAsync(pop->vbuf[1], pop->vbuf[0], sizeof(float4) * pop->total_slots, hipMemcpyDeviceToDevice,
-                             pop->st));
     pop->h_step = 0;
-    pop->h_step_stage = 0;
-    HIPC(pop, hipMemcpyAsync(pop->d_step, &pop->h_step_stage, sizeof(int64_t), hipMemcpyHostToDevice, pop->st));
     pop->rec_valid = pop->ck_every > 0;
-    std::vector<uint8_t> bad(pop->R);
-    HIPC(pop, hipMemcpyAsync(bad.data(), pop->bad_class, pop->R, hipMemcpyDeviceToHost, pop->st));
+    HIPC(pop, launch_finish_build(pop->d_robots, pop->R, pop->bad_class, pop->d_mass_off, pop->d_spring_off,
+                                  pop->d_step, pop->h_built, pop->st));
     HIPC(pop, hipStreamSynchronize(pop->st));
-    pop->counts_valid = false;
-    for (int r = 0; r < pop->R; ++r)
-        if (bad[r]) {
-            pop->built = false;
-            HIPC(pop, hipMemsetAsync(pop->bad_class, 0, pop->R, pop->st));
-            return set_err(SR_EINVAL, "robot %d has a voxel class outside 0..4", r);
-        }
-    pop->built = true;
+    pop->built = pop->h_built[0] < 0;
+    if (!pop->built) return set_err(SR_EINVAL, "robot %d has a voxel class outside 0..4", (int)pop->h_built[0]);
     pop->vox_ok = true;
     return SR_OK;
 }
@@ -407,27 +379,27 @@ int pop_create(const sr_sim_params *params, int32_t n_robots, const int32_t *gri
     const size_t S = slots, P = slots * NDIR;
     hipError_t e = hipSuccess;
 #define ALLOC(ptr, cnt) \
-    if (e == hipSuccess) e = dalloc(&(ptr), (cnt))
+    do {                \
+        if (e == hipSuccess) e = dalloc(&(ptr), (cnt)); \
+    } while (0)
     ALLOC(pop->d_robots, (size_t)n_robots);
     ALLOC(pop->kept, (size_t)vox);
     ALLOC(pop->w, (size_t)vox);
     ALLOC(pop->pl.k, P);
-    ALLOC(pop->pl.kL0, P);
     ALLOC(pop->pl.kal, P);
     ALLOC(pop->pl.kbe, P);
-    ALLOC(pop->pl.kd, P);
+    // the adjoint's velocity form reads the dashpot plane for a damped ground too
+    if (pop->dash || pop->c.gdamp) ALLOC(pop->pl.kd, P);
     ALLOC(pop->pl.vkp, S);
-    ALLOC(pop->sid, P);
+    ALLOC(pop->ix.base, S);
+    ALLOC(pop->ix.mask, S);
     ALLOC(pop->x0, S);
     ALLOC(pop->xbuf[0], S);
     ALLOC(pop->xbuf[1], S);
     ALLOC(pop->vbuf[0], S);
     ALLOC(pop->vbuf[1], S);
     ALLOC(pop->slot_node, S);
-    ALLOC(pop->node_slot, S);
     ALLOC(pop->slot_robot, S);
-    ALLOC(pop->rows, S);
-    ALLOC(pop->entries, 2 * P);
     ALLOC(pop->bad_class, (size_t)n_robots);
     ALLOC(pop->diverged, (size_t)n_robots);
     ALLOC(pop->d_step, 1);
@@ -435,9 +407,10 @@ int pop_create(const sr_sim_params *params, int32_t n_robots, const int32_t *gri
     ALLOC(pop->d_mass_off, (size_t)n_robots + 1);
     ALLOC(pop->d_spring_off, (size_t)n_robots + 1);
     ALLOC(pop->q_cls, (size_t)vox);
-    ALLOC(pop->q_w, (size_t)vox);
     ALLOC(pop->vox_robot, (size_t)vox);
 #undef ALLOC
+    if (e == hipSuccess)
+        e = hipHostMalloc(reinterpret_cast<void **>(&pop->h_built), sizeof(int64_t) * (2 * (size_t)n_robots + 3));
     if (e != hipSuccess) {
         pop_free(pop);
         delete pop;
@@ -495,6 +468,9 @@ int pop_create(const sr_sim_params *params, int32_t n_robots, const int32_t *gri
         e = hipMemcpyAsync(pop->d_lists, lists.data(), sizeof(int32_t) * n_robots, hipMemcpyHostToDevice, pop->st);
     if (e == hipSuccess) e = hipMemsetAsync(pop->bad_class, 0, n_robots, pop->st);
     if (e == hipSuccess) e = hipMemsetAsync(pop->diverged, 0, n_robots, pop->st);
+    // written only when there are phases / dashpots
+    if (e == hipSuccess) e = hipMemsetAsync(pop->pl.kbe, 0, sizeof(float) * P, pop->st);
+    if (e == hipSuccess && pop->pl.kd) e = hipMemsetAsync(pop->pl.kd, 0, sizeof(float) * P, pop->st);
     if (e == hipSuccess) e = hipStreamSynchronize(pop->st);
     if (e != hipSuccess) rc = set_err(SR_EHIP, "create: %s", hipGetErrorString(e));
     if (rc != SR_OK) {
@@ -519,10 +495,11 @@ int pop_build_from_voxels(sr_pop *pop, const uint8_t *cls, const float *w) {
     if (!cls || !w) return set_err(SR_EINVAL, "null voxel array");
     if (cls != pop->q_cls)
         HIPC(pop, hipMemcpyAsync(pop->q_cls, cls, pop->total_vox, hipMemcpyDeviceToDevice, pop->st));
-    HIPC(pop, hipMemcpyAsync(pop->w, w, sizeof(float) * pop->total_vox, hipMemcpyDeviceToDevice, pop->st));
-    HIPC(pop, launch_build_mesh(pop->d_robots, pop->R, SR_MAX_SIDE, pop->p, cls, pop->w, pop->kept, pop->pl, pop->sid,
-                                pop->x0, pop->xbuf[0], pop->vbuf[0], pop->slot_node, pop->node_slot, pop->rows,
-                                pop->entries, pop->bad_class, pop->diverged, pop->st));
+    if (w != pop->w)
+        HIPC(pop, hipMemcpyAsync(pop->w, w, sizeof(float) * pop->total_vox, hipMemcpyDeviceToDevice, pop->st));
+    HIPC(pop, launch_build_mesh(pop->d_robots, pop->R, pop->max_side, pop->phase || pop->dash, pop->p, cls, pop->w,
+                                pop->kept, pop->pl, pop->ix, pop->x0, pop->xbuf[0], pop->vbuf[0], pop->slot_node,
+                                pop->bad_class, pop->diverged, pop->st));
     return finish_build(pop);
 }
 
@@ -531,8 +508,8 @@ int pop_build_from_genomes(sr_pop *pop, const float *genomes, const float *B, in
     if (!genomes || !B) return set_err(SR_EINVAL, "null genome or B");
     if (precision != SR_QUERY_FP32 && precision != SR_QUERY_BF16)
         return set_err(SR_EINVAL, "unknown query precision %d", precision);
-    HIPC(pop, launch_query(pop->d_robots, pop->R, pop->max_side, genomes, B, precision, pop->q_cls, pop->q_w, pop->st));
-    return pop_build_from_voxels(pop, pop->q_cls, pop->q_w);
+    HIPC(pop, launch_query(pop->d_robots, pop->R, pop->max_side, genomes, B, precision, pop->q_cls, pop->w, pop->st));
+    return pop_build_from_voxels(pop, pop->q_cls, pop->w);
 }
 
 int pop_set_step_config(sr_pop *pop, int32_t mode, int32_t block, int32_t steps_per_launch) {
@@ -633,7 +610,7 @@ int enqueue_steps(sr_pop *pop, int n_steps, float2 *sc, hipStream_t st) {
     if (pop->mode == SR_STEP_PLAIN) {
         for (int t = 0; t < n_steps; ++t) {
             const int a = pop->cur, b = 1 - pop->cur;
-            HIPC(pop, launch_plain_step(pop->d_robots, pop->R, pop->total_slots, pop->rows, pop->entries, pop->pl,
+            HIPC(pop, launch_plain_step(pop->d_robots, pop->total_slots, pop->ix, pop->pl,
                                         pop->xbuf[a], pop->vbuf[a], pop->xbuf[b], pop->vbuf[b], sc, t,
                                         pop->phase, pop->diverged, pop->slot_robot, pop->c, st));
             pop->cur = b;
@@ -711,7 +688,7 @@ int recorded_steps(sr_pop *pop, int n_steps, float2 *sc) {
         if (pop->mode == SR_STEP_PLAIN) {
             for (int q = 0; q < len; ++q) {
                 const int a = pop->cur, b = 1 - pop->cur;
-                HIPC(pop, launch_plain_step(pop->d_robots, pop->R, pop->total_slots, pop->rows, pop->entries, pop->pl,
+                HIPC(pop, launch_plain_step(pop->d_robots, pop->total_slots, pop->ix, pop->pl,
                                             pop->xbuf[a], pop->vbuf[a], pop->xbuf[b], pop->vbuf[b], sc, t + q,
                                             pop->phase, pop->diverged, pop->slot_robot, pop->c, pop->st));
                 pop->cur = b;
@@ -804,14 +781,13 @@ int pop_fitness(sr_pop *pop, float *fitness) {
 int pop_get_counts(sr_pop *pop, int32_t *n_masses, int32_t *n_springs, int64_t *mass_offset, int64_t *spring_offset) {
     CHECK_POP(pop);
     if (!pop->built) return set_err(SR_ESTATE, "pop_get_counts before a build");
-    int rc = ensure_counts(pop);
-    if (rc) return rc;
+    const int64_t *mo = ::mass_off(pop), *so = ::spring_off(pop);
     for (int r = 0; r < pop->R; ++r) {
-        if (n_masses) n_masses[r] = pop->h_robots[r].M;
-        if (n_springs) n_springs[r] = pop->h_robots[r].S;
+        if (n_masses) n_masses[r] = (int32_t)(mo[r + 1] - mo[r]);
+        if (n_springs) n_springs[r] = (int32_t)(so[r + 1] - so[r]);
     }
-    if (mass_offset) memcpy(mass_offset, pop->h_mass_off.data(), sizeof(int64_t) * (pop->R + 1));
-    if (spring_offset) memcpy(spring_offset, pop->h_spring_off.data(), sizeof(int64_t) * (pop->R + 1));
+    if (mass_offset) memcpy(mass_offset, mo, sizeof(int64_t) * (pop->R + 1));
+    if (spring_offset) memcpy(spring_offset, so, sizeof(int64_t) * (pop->R + 1));
     return SR_OK;
 }
 
@@ -834,9 +810,7 @@ int pop_get_query(sr_pop *pop, uint8_t *cls, float *w) {
 int pop_get_springs(sr_pop *pop, int32_t *ij, float *L0, float *k, float *a, float *phi) {
     CHECK_POP(pop);
     if (!pop->built) return set_err(SR_ESTATE, "pop_get_springs before a build");
-    int rc = ensure_counts(pop);
-    if (rc) return rc;
-    HIPC(pop, launch_springs_io(pop->d_robots, pop->R, pop->total_slots, pop->slot_robot, pop->slot_node, pop->sid,
+    HIPC(pop, launch_springs_io(pop->d_robots, pop->R, pop->total_slots, pop->slot_robot, pop->slot_node, pop->ix,
                                 pop->d_spring_off, pop->pl, pop->p.voxel_len, ij, L0, k, a, phi, nullptr, nullptr,
                                 nullptr, 0, pop->st));
     return SR_OK;
@@ -845,8 +819,6 @@ int pop_get_springs(sr_pop *pop, int32_t *ij, float *L0, float *k, float *a, flo
 int pop_set_spring_params(sr_pop *pop, const float *k, const float *a, const float *phi) {
     CHECK_POP(pop);
     if (!pop->built) return set_err(SR_ESTATE, "pop_set_spring_params before a build");
-    int rc = ensure_counts(pop);
-    if (rc) return rc;
     if (phi && !pop->phase) {
         // the captured step graphs hold the kernels without the phase plane
         pop->phase = true;
@@ -860,7 +832,7 @@ int pop_set_spring_params(sr_pop *pop, const float *k, const float *a, const flo
             g.cfg.block = persist_default_block(g.n, pop->dash, false, &g.cfg.variant);
             clear_graphs(pop);
         }
-    HIPC(pop, launch_springs_io(pop->d_robots, pop->R, pop->total_slots, pop->slot_robot, pop->slot_node, pop->sid,
+    HIPC(pop, launch_springs_io(pop->d_robots, pop->R, pop->total_slots, pop->slot_robot, pop->slot_node, pop->ix,
                                 pop->d_spring_off, pop->pl, pop->p.voxel_len, nullptr, nullptr, nullptr, nullptr,
                                 nullptr, k, a, phi, 1, pop->st));
     return SR_OK;
@@ -869,8 +841,6 @@ int pop_set_spring_params(sr_pop *pop, const float *k, const float *a, const flo
 int pop_get_state(sr_pop *pop, float *x, float *v, int64_t *step) {
     CHECK_POP(pop);
     if (!pop->built) return set_err(SR_ESTATE, "pop_get_state before a build");
-    int rc = ensure_counts(pop);
-    if (rc) return rc;
     HIPC(pop, launch_gather_state(pop->d_robots, pop->R, pop->total_slots, pop->slot_robot, pop->slot_node,
                                   pop->d_mass_off, pop->xbuf[pop->cur], pop->vbuf[pop->cur], x, v, 0, pop->st));
     if (step) *step = pop->h_step;
@@ -881,8 +851,6 @@ int pop_set_state(sr_pop *pop, const float *x, const float *v, int64_t step) {
     CHECK_POP(pop);
     if (!pop->built) return set_err(SR_ESTATE, "pop_set_state before a build");
     if (step < 0) return set_err(SR_EINVAL, "step < 0");
-    int rc = ensure_counts(pop);
-    if (rc) return rc;
     HIPC(pop, launch_gather_state(pop->d_robots, pop->R, pop->total_slots, pop->slot_robot, pop->slot_node,
                                   pop->d_mass_off, pop->xbuf[pop->cur], pop->vbuf[pop->cur], const_cast<float *>(x),
                                   const_cast<float *>(v), 1, pop->st));
@@ -906,18 +874,10 @@ int pop_get_status(sr_pop *pop, uint8_t *diverged) {
 int pop_reset(sr_pop *pop) {
     CHECK_POP(pop);
     if (!pop->built) return set_err(SR_ESTATE, "pop_reset before a build");
-    HIPC(pop, hipMemcpyAsync(pop->xbuf[0], pop->x0, sizeof(float4) * pop->total_slots, hipMemcpyDeviceToDevice, pop->st));
-    HIPC(pop, hipMemsetAsync(pop->vbuf[0], 0, sizeof(float4) * pop->total_slots, pop->st));
-    HIPC(pop, hipMemsetAsync(pop->diverged, 0, pop->R, pop->st));
+    HIPC(pop, launch_reset(pop->total_slots, pop->R, pop->x0, pop->xbuf[0], pop->vbuf[0], pop->diverged, pop->d_step,
+                           pop->st));
     pop->cur = 0;
-    HIPC(pop, hipMemcpyAsync(pop->xbuf[1], pop->xbuf[0], sizeof(float4) * pop->total_slots, hipMemcpyDeviceToDevice,
-                             pop->st));
-    HIPC(pop, hipMemcpyAsync(pop->vbuf[1], pop->vbuf[0], sizeof(float4) * pop->total_slots, hipMemcpyDeviceToDevice,
-                             pop->st));
     pop->h_step = 0;
-    pop->h_step_stage = 0;
-    HIPC(pop, hipMemcpyAsync(pop->d_step, &pop->h_step_stage, sizeof(int64_t), hipMemcpyHostToDevice, pop->st));
-    HIPC(pop, hipStreamSynchronize(pop->st));
     pop->rec_valid = pop->ck_every > 0;
     return SR_OK;
 }
@@ -1003,8 +963,6 @@ int pop_backward(sr_pop *pop, const float *dJ_dfitness, float *g_k, float *g_a, 
     const int K = pop->ck_every;
     int rc = ensure_adj_scratch(pop, K);
     if (rc) return rc;
-    rc = ensure_counts(pop);
-    if (rc) return rc;
     const double omega_dt = 2.0 * M_PI * (double)pop->p.act_freq * pop->p.dt;
     HIPC(pop, launch_adj_init(pop->d_robots, pop->total_slots, pop->slot_robot, pop->x0, dJ_dfitness, pop->lx, pop->lv,
                               pop->gk, pop->gs, pop->gc, pop->gd, pop->st));
@@ -1069,7 +1027,7 @@ int pop_backward(sr_pop *pop, const float *dJ_dfitness, float *g_k, float *g_a, 
         }
     }
     if (split && nseg > 0) HIPC(pop, hipStreamWaitEvent(pop->st, ev_grd[0], 0));  // segment 0's sums
-    HIPC(pop, launch_adj_springs(pop->d_robots, pop->total_slots, pop->slot_robot, pop->sid, pop->d_spring_off, pop->pl,
+    HIPC(pop, launch_adj_springs(pop->d_robots, pop->total_slots, pop->slot_robot, pop->ix, pop->d_spring_off, pop->pl,
                                  pop->p.voxel_len, pop->gk, pop->gs, pop->gc, g_k, g_a, g_phi, pop->st));
     if (g_genome)
         HIPC(pop, launch_adj_genome(pop->d_robots, pop->R, pop->total_vox, pop->vox_robot, pop->kept, pop->w, pop->pl,

@@ -64,67 +64,77 @@ __global__ void k_advance(int64_t *d_step, int n) {
 }
 
 // ---------------------------------------------------------------- per-step form
-// One thread per node; positions and velocities in HBM, one launch per step.
-// The node gathers over its incidence row (forward springs, then backward
-// springs), recomputing every spring force it touches.  DASH adds the spring
-// dashpots (neighbour velocities read from HBM too).
+// One thread per lattice slot; positions and velocities in HBM, one launch per
+// step.  A node gathers over its existing springs (forward directions, then
+// backward ones), recomputing every spring force it touches; neighbour slots
+// are consecutive across lanes, so every read is coalesced.  Absent slots and
+// diverged robots carry their state over.  DASH adds the spring dashpots
+// (neighbour velocities read from HBM too).
+template <bool PHASE, bool DASH>
+__device__ __forceinline__ void plain_spring(const Planes &pl, int pi, float L0, float2 sc, const float4 &X,
+                                             const float4 &V, const float4 *x, const float4 *v, int nbr, float3 &F) {
+    const float4 Y = x[nbr];
+    const float dx = Y.x - X.x, dy = Y.y - X.y, dz = Y.z - X.z;
+    const float k = pl.k[pi];
+    float cf;
+    if constexpr (DASH) {
+        const float4 VY = v[nbr];
+        cf = spring_coef_d<PHASE>(k, k * L0, pl.kal[pi], PHASE ? pl.kbe[pi] : 0.f, sc.x, sc.y, len2(dx, dy, dz),
+                                  pl.kd[pi], rate(VY.x - V.x, VY.y - V.y, VY.z - V.z, dx, dy, dz));
+    } else {
+        cf = spring_coef<PHASE>(k, k * L0, pl.kal[pi], PHASE ? pl.kbe[pi] : 0.f, sc.x, sc.y, len2(dx, dy, dz));
+    }
+    F.x = fmaf(cf, dx, F.x);
+    F.y = fmaf(cf, dy, F.y);
+    F.z = fmaf(cf, dz, F.z);
+}
+
 template <bool PHASE, bool DASH>
 __global__ __launch_bounds__(256) void k_plain(const RobotInfo *robots, int total_slots, const int32_t *slot_robot,
-                                               const NodeRow *rows, const Entry *entries, Planes pl,
-                                               const float4 *__restrict__ x, const float4 *__restrict__ v,
-                                               float4 *__restrict__ xn, float4 *__restrict__ vn,
-                                               const float2 *sc_tab, int t, const uint8_t *diverged, SimConst c) {
+                                               SpringIndex ix, Planes pl, const float4 *__restrict__ x,
+                                               const float4 *__restrict__ v, float4 *__restrict__ xn,
+                                               float4 *__restrict__ vn, const float2 *sc_tab, int t,
+                                               const uint8_t *diverged, SimConst c) {
     const int g = blockIdx.x * blockDim.x + threadIdx.x;
     const float2 sc = sc_tab[t];
     if (g >= total_slots) return;
     const int r = slot_robot[g];
     const RobotInfo ri = robots[r];
-    if (g - ri.slot_base >= ri.M || diverged[r]) return;
-    const NodeRow row = rows[g];
-    const float4 X = x[row.gslot];
-    const float4 V = v[row.gslot];
-    float3 Ff = make_float3(0.f, 0.f, 0.f), Fb = make_float3(0.f, 0.f, 0.f);
-    for (int e = row.start; e < row.mid; ++e) {
-        const Entry E = entries[e];
-        const float4 Y = x[E.nbr];
-        const float dx = Y.x - X.x, dy = Y.y - X.y, dz = Y.z - X.z;
-        float cf;
-        if constexpr (DASH) {
-            const float4 VY = v[E.nbr];
-            cf = spring_coef_d<PHASE>(pl.k[E.plane], pl.kL0[E.plane], pl.kal[E.plane], PHASE ? pl.kbe[E.plane] : 0.f,
-                                      sc.x, sc.y, len2(dx, dy, dz), pl.kd[E.plane],
-                                      rate(VY.x - V.x, VY.y - V.y, VY.z - V.z, dx, dy, dz));
-        } else {
-            cf = spring_coef<PHASE>(pl.k[E.plane], pl.kL0[E.plane], pl.kal[E.plane], PHASE ? pl.kbe[E.plane] : 0.f,
-                                    sc.x, sc.y, len2(dx, dy, dz));
-        }
-        Ff.x = fmaf(cf, dx, Ff.x);
-        Ff.y = fmaf(cf, dy, Ff.y);
-        Ff.z = fmaf(cf, dz, Ff.z);
+    const float4 X = x[g], V = v[g];
+    if (X.w == 0.f || diverged[r]) {
+        xn[g] = X;
+        vn[g] = V;
+        return;
     }
-    for (int e = row.mid; e < row.end; ++e) {
-        const Entry E = entries[e];
-        const float4 Y = x[E.nbr];
-        const float dx = Y.x - X.x, dy = Y.y - X.y, dz = Y.z - X.z;
-        float cf;
-        if constexpr (DASH) {
-            const float4 VY = v[E.nbr];
-            cf = spring_coef_d<PHASE>(pl.k[E.plane], pl.kL0[E.plane], pl.kal[E.plane], PHASE ? pl.kbe[E.plane] : 0.f,
-                                      sc.x, sc.y, len2(dx, dy, dz), pl.kd[E.plane],
-                                      rate(VY.x - V.x, VY.y - V.y, VY.z - V.z, dx, dy, dz));
-        } else {
-            cf = spring_coef<PHASE>(pl.k[E.plane], pl.kL0[E.plane], pl.kal[E.plane], PHASE ? pl.kbe[E.plane] : 0.f,
-                                    sc.x, sc.y, len2(dx, dy, dz));
-        }
-        Fb.x = fmaf(cf, dx, Fb.x);
-        Fb.y = fmaf(cf, dy, Fb.y);
-        Fb.z = fmaf(cf, dz, Fb.z);
+    const int N = ri.N, s = g - ri.slot_base, pself = NDIR * ri.slot_base + s;
+    const unsigned fwd = ix.mask[g];
+    float3 Ff = make_float3(0.f, 0.f, 0.f), Fb = make_float3(0.f, 0.f, 0.f);
+#pragma unroll
+    for (int d = 0; d < NDIR; ++d)
+        if (fwd >> d & 1u)
+            plain_spring<PHASE, DASH>(pl, pself + d * ri.slots, L0d(c, d), sc, X, V, x, v, g + dir_off(d, N), Ff);
+#pragma unroll
+    for (int d = 0; d < NDIR; ++d) {
+        // the lower slot of a wrapped-around neighbour has no spring that leaves the lattice
+        const int off = dir_off(d, N);
+        if (s >= off && (ix.mask[g - off] >> d & 1u))
+            plain_spring<PHASE, DASH>(pl, pself + d * ri.slots - off, L0d(c, d), sc, X, V, x, v, g - off, Fb);
     }
     float3 xs = make_float3(X.x, X.y, X.z);
     float3 vs = make_float3(V.x, V.y, V.z);
     integrate_node(c, xs, vs, Ff, Fb);
-    xn[row.gslot] = make_float4(xs.x, xs.y, xs.z, 1.f);
-    vn[row.gslot] = make_float4(vs.x, vs.y, vs.z, 0.f);
+    xn[g] = make_float4(xs.x, xs.y, xs.z, 1.f);
+    vn[g] = make_float4(vs.x, vs.y, vs.z, 0.f);
+}
+
+__global__ __launch_bounds__(256) void k_reset(int total_slots, int R, const float4 *x0, float4 *x, float4 *v,
+                                               uint8_t *diverged, int64_t *step) {
+    const int g = blockIdx.x * 256 + threadIdx.x;
+    if (g == 0) *step = 0;
+    if (g < R) diverged[g] = 0;  // a robot has at least 8 slots
+    if (g >= total_slots) return;
+    x[g] = x0[g];
+    v[g] = make_float4(0.f, 0.f, 0.f, 0.f);
 }
 
 __global__ __launch_bounds__(256) void k_check_div(const RobotInfo *robots, const float4 *x, const float4 *v,
@@ -1084,55 +1094,46 @@ __global__ void k_gather_state(const RobotInfo *robots, int total_slots, const i
     }
 }
 
-__global__ void k_springs_io(const RobotInfo *robots, int total_slots, const int32_t *slot_robot,
-                             const int32_t *slot_node, const int32_t *sid, const int64_t *spring_off, Planes pl,
-                             float voxel_len, int32_t *ij, float *L0o, float *ko, float *ao, float *phio,
-                             const float *kin, const float *ain, const float *phin, int write) {
-    const int g = blockIdx.x * blockDim.x + threadIdx.x;
-    if (g >= total_slots) return;
-    const int r = slot_robot[g];
-    const RobotInfo ri = robots[r];
-    const int s = g - ri.slot_base;
-    for (int d = 0; d < NDIR; ++d) {
-        const int pi = NDIR * ri.slot_base + d * ri.slots + s;
-        const int id = sid[pi];
-        if (id < 0) continue;
-        const int64_t o = spring_off[r] + id;
+// a spring's amplitude and phase from its planes (signed amplitude and zero
+// phase when every term is in phase)
+__device__ __forceinline__ void spring_polar(float kL0, float kal, float kbe, float &a, float &ph) {
+    a = 0.f;
+    ph = 0.f;
+    if (kL0 != 0.f) {
+        if (kbe == 0.f) a = kal / kL0;
+        else {
+            a = sqrtf(kal * kal + kbe * kbe) / kL0;
+            ph = atan2f(kbe, kal);
+        }
+    }
+}
+
+// The springs in canonical order: 24 B each, at the rate of memory.
+__global__ __launch_bounds__(EACH_SLOTS) void k_springs_io(const RobotInfo *robots, int total_slots,
+                                                           const int32_t *slot_robot, const int32_t *slot_node,
+                                                           SpringIndex ix, const int64_t *spring_off, Planes pl,
+                                                           float voxel_len, int32_t *ij, float *L0o, float *ko,
+                                                           float *ao, float *phio, const float *kin, const float *ain,
+                                                           const float *phin, int write) {
+    each_spring(robots, total_slots, slot_robot, ix, spring_off, [&](int64_t o, int g, int d, int pi, int N) {
         const float L0 = voxel_len * sqrtf((float)dir_len2(d));
+        float k = pl.k[pi], a, ph;
+        spring_polar(k * L0, pl.kal[pi], pl.kbe[pi], a, ph);
         if (!write) {
             if (ij) {
                 ij[2 * o] = slot_node[g];
-                ij[2 * o + 1] = slot_node[g + dir_off(d, ri.N)];
+                ij[2 * o + 1] = slot_node[g + dir_off(d, N)];
             }
             if (L0o) L0o[o] = L0;
-            const float k = pl.k[pi], kL0 = pl.kL0[pi], kal = pl.kal[pi], kbe = pl.kbe[pi];
-            float a = 0.f, ph = 0.f;
-            if (kL0 != 0.f) {
-                if (kbe == 0.f) a = kal / kL0;
-                else {
-                    a = sqrtf(kal * kal + kbe * kbe) / kL0;
-                    ph = atan2f(kbe, kal);
-                }
-            }
             if (ko) ko[o] = k;
             if (ao) ao[o] = a;
             if (phio) phio[o] = ph;
         } else {
-            // read the current values for fields that are not given
-            float k = pl.k[pi], kL0 = pl.kL0[pi], kal = pl.kal[pi], kbe = pl.kbe[pi];
-            float a = 0.f, ph = 0.f;
-            if (kL0 != 0.f) {
-                if (kbe == 0.f) a = kal / kL0;
-                else {
-                    a = sqrtf(kal * kal + kbe * kbe) / kL0;
-                    ph = atan2f(kbe, kal);
-                }
-            }
+            // fields that are not given keep their current values
             if (kin) k = kin[o];
             if (ain) a = ain[o];
             if (phin) ph = phin[o];
             pl.k[pi] = k;
-            pl.kL0[pi] = k * L0;
             if (ph == 0.f) {
                 pl.kal[pi] = k * L0 * a;
                 pl.kbe[pi] = 0.f;
@@ -1141,7 +1142,7 @@ __global__ void k_springs_io(const RobotInfo *robots, int total_slots, const int
                 pl.kbe[pi] = k * L0 * a * sinf(ph);
             }
         }
-    }
+    });
 }
 
 // ---------------------------------------------------------------- persistent dispatch table
@@ -1460,15 +1461,20 @@ hipError_t launch_advance(int64_t *d_step, int n, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t launch_plain_step(const RobotInfo *robots, int R, int total_slots, const NodeRow *rows, const Entry *entries,
-                             Planes pl, const float4 *x, const float4 *v, float4 *xn, float4 *vn, const float2 *sc,
-                             int t, bool phase, const uint8_t *diverged, const int32_t *slot_robot, SimConst c,
-                             hipStream_t st) {
-    (void)R;
+hipError_t launch_plain_step(const RobotInfo *robots, int total_slots, SpringIndex ix, Planes pl, const float4 *x,
+                             const float4 *v, float4 *xn, float4 *vn, const float2 *sc, int t, bool phase,
+                             const uint8_t *diverged, const int32_t *slot_robot, SimConst c, hipStream_t st) {
     auto fn = c.dash ? (phase ? k_plain<true, true> : k_plain<false, true>)
                      : (phase ? k_plain<true, false> : k_plain<false, false>);
-    hipLaunchKernelGGL(fn, dim3((total_slots + 255) / 256), dim3(256), 0, st, robots, total_slots, slot_robot, rows,
-                       entries, pl, x, v, xn, vn, sc, t, diverged, c);
+    hipLaunchKernelGGL(fn, dim3((total_slots + 255) / 256), dim3(256), 0, st, robots, total_slots, slot_robot, ix, pl,
+                       x, v, xn, vn, sc, t, diverged, c);
+    return hipGetLastError();
+}
+
+hipError_t launch_reset(int total_slots, int R, const float4 *x0, float4 *x, float4 *v, uint8_t *diverged,
+                        int64_t *step, hipStream_t st) {
+    hipLaunchKernelGGL(k_reset, dim3((total_slots + 255) / 256), dim3(256), 0, st, total_slots, R, x0, x, v, diverged,
+                       step);
     return hipGetLastError();
 }
 
@@ -1495,12 +1501,12 @@ hipError_t launch_gather_state(const RobotInfo *robots, int R, int total_slots, 
 }
 
 hipError_t launch_springs_io(const RobotInfo *robots, int R, int total_slots, const int32_t *slot_robot,
-                             const int32_t *slot_node, const int32_t *sid, const int64_t *spring_off, Planes pl,
+                             const int32_t *slot_node, SpringIndex ix, const int64_t *spring_off, Planes pl,
                              float voxel_len, int32_t *ij, float *L0, float *k, float *a, float *phi,
                              const float *k_in, const float *a_in, const float *phi_in, int write, hipStream_t st) {
     (void)R;
-    hipLaunchKernelGGL(k_springs_io, dim3((total_slots + 255) / 256), dim3(256), 0, st, robots, total_slots,
-                       slot_robot, slot_node, sid, spring_off, pl, voxel_len, ij, L0, k, a, phi, k_in, a_in, phi_in,
+    hipLaunchKernelGGL(k_springs_io, dim3((total_slots + EACH_SLOTS - 1) / EACH_SLOTS), dim3(EACH_SLOTS), 0, st, robots, total_slots,
+                       slot_robot, slot_node, ix, spring_off, pl, voxel_len, ij, L0, k, a, phi, k_in, a_in, phi_in,
                        write);
     return hipGetLastError();
 }
