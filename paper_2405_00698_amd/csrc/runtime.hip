@@ -1,4 +1,5 @@
 // runtime.hip -- population handle, memory plan and the C ABI of softrobot.h.
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -35,6 +36,7 @@ static __device__ __align__(256) float2 scratch[SR_NOALLOC_MAX_STEPS];
 namespace {
 constexpr int kMaxDevices = 64;
 constexpr int NSET = 3;  // segment buffer sets of the adjoint pipeline
+constexpr int REC_LANES = 4;  // side groups of a recorded run or a reverse sweep at once
 std::mutex g_scratch_mu;
 float2 *g_scratch[kMaxDevices] = {};
 
@@ -125,13 +127,16 @@ struct sr_pop {
     float4 *rec_x[NSET] = {}, *rec_v[NSET] = {};
     float4 *rec_u[NSET] = {};  // v_n per step (dashpots or a damped ground)
     float4 *rec_l[NSET] = {};  // lambda_F per step (split adjoint of the largest sides)
-    float4 *tmp_x[NSET] = {}, *tmp_v[NSET] = {};
     float4 *lx = nullptr, *lv = nullptr;
     float *gk = nullptr, *gs = nullptr, *gc = nullptr, *gd = nullptr, *dJdw = nullptr;
-    float2 *sc_seg[NSET] = {};
-    hipStream_t adj_st = nullptr, adj_gst = nullptr;  // recomputation; gradient passes (split form)
-    // start, recorded[NSET], reversed[NSET], gradient sums formed[NSET]
-    hipEvent_t adj_ev[1 + 3 * NSET] = {};
+    float2 *adj_sc = nullptr;  // time table of the whole recorded run
+    int adj_sc_cap = 0;
+    // start, then per group recorded[NSET], reversed[NSET], gradient sums formed[NSET]
+    std::vector<hipEvent_t> adj_ev;
+    // lanes of the recorded forward and the reverse sweep: private streams, the
+    // groups in launch order and the lane of each
+    std::vector<hipStream_t> rec_st;
+    std::vector<int> rec_order, rec_lane;
     // captured step graphs: one per (n_steps, mode, current buffer, steps per launch)
     bool use_graphs = true;
     hipStream_t cap = nullptr;
@@ -174,6 +179,7 @@ void clear_graphs(sr_pop *pop) {
 void pop_free(sr_pop *pop) {
     clear_graphs(pop);
     for (auto s : pop->side) (void)hipStreamDestroy(s);
+    for (auto s : pop->rec_st) (void)hipStreamDestroy(s);
     for (auto e : pop->ev) (void)hipEventDestroy(e);
     if (pop->cap) (void)hipStreamDestroy(pop->cap);
     void *ptrs[] = {pop->d_robots, pop->kept, pop->w, pop->pl.k, pop->pl.kal, pop->pl.kbe, pop->pl.kd, pop->pl.vkp,
@@ -181,25 +187,32 @@ void pop_free(sr_pop *pop) {
                     pop->slot_node, pop->slot_robot,
                     pop->bad_class, pop->diverged, pop->d_step, pop->sc, pop->d_lists, pop->d_mass_off,
                     pop->d_spring_off, pop->q_cls, pop->vox_robot, pop->ck_x, pop->ck_v,
-                    pop->lx, pop->lv, pop->gk, pop->gs, pop->gc, pop->gd, pop->dJdw};
+                    pop->lx, pop->lv, pop->gk, pop->gs, pop->gc, pop->gd, pop->dJdw, pop->adj_sc};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     for (int b = 0; b < NSET; ++b) {
-        void *seg[] = {pop->rec_x[b], pop->rec_v[b], pop->rec_u[b], pop->rec_l[b], pop->tmp_x[b], pop->tmp_v[b],
-                       pop->sc_seg[b]};
+        void *seg[] = {pop->rec_x[b], pop->rec_v[b], pop->rec_u[b], pop->rec_l[b]};
         for (void *p : seg)
             if (p) (void)hipFree(p);
     }
     if (pop->h_built) (void)hipHostFree(pop->h_built);
-    for (auto e : pop->adj_ev)
-        if (e) (void)hipEventDestroy(e);
-    if (pop->adj_st) (void)hipStreamDestroy(pop->adj_st);
-    if (pop->adj_gst) (void)hipStreamDestroy(pop->adj_gst);
+    for (auto e : pop->adj_ev) (void)hipEventDestroy(e);
 }
 
 // node and spring offsets of the last build, host copies
 const int64_t *mass_off(const sr_pop *pop) { return pop->h_built + 1; }
 const int64_t *spring_off(const sr_pop *pop) { return pop->h_built + 2 + pop->R; }
+
+// n private streams (default priority)
+hipError_t add_streams(std::vector<hipStream_t> &to, int n) {
+    while ((int)to.size() < n) {
+        hipStream_t st;
+        const hipError_t e = hipStreamCreateWithFlags(&st, hipStreamNonBlocking);
+        if (e != hipSuccess) return e;
+        to.push_back(st);
+    }
+    return hipSuccess;
+}
 
 int ensure_sc(sr_pop *pop, int n) {
     if (n <= pop->sc_cap) return SR_OK;
@@ -443,15 +456,37 @@ int pop_create(const sr_sim_params *params, int32_t n_robots, const int32_t *gri
             pop->lane[G - 1 - q] = q;
         }
     }
+    // Recorded runs and reverse sweeps: the groups dealt, longest first, to the
+    // least loaded of REC_LANES streams, a group's time taken as its lattice
+    // points times its turns on 256 CUs.  Four lanes are what the device's four
+    // hardware queues run at once; a stream beyond them only waits behind
+    // another one.  From three groups on the last lane also carries the gradient
+    // passes of the reverse sweep (about a quarter of its time).
+    {
+        const int G = (int)pop->groups.size();
+        auto cost = [&](int g) {
+            const double N = pop->groups[g].n + 1;
+            return N * N * N * ((pop->groups[g].count + 255) / 256);
+        };
+        double load[REC_LANES] = {};
+        for (int g = 0; g < G; ++g) {
+            pop->rec_order.push_back(g);
+            if (G >= 3 && adjoint_is_split(pop->groups[g].n, pop->c.dash || pop->c.gdamp))
+                load[REC_LANES - 1] += 0.25 * cost(g);
+        }
+        std::stable_sort(pop->rec_order.begin(), pop->rec_order.end(), [&](int a, int b) { return cost(a) > cost(b); });
+        pop->rec_lane.assign(G, 0);
+        for (int g : pop->rec_order) {
+            const int l = (int)(std::min_element(load, load + REC_LANES) - load);
+            pop->rec_lane[g] = l;
+            load[l] += cost(g);
+        }
+    }
     int rc = SR_OK;
     // private streams (default priority) for capturing step graphs: one per
     // extra size group, so the groups become parallel branches of one graph
-    e = hipStreamCreateWithFlags(&pop->cap, hipStreamNonBlocking);
-    for (size_t g = 0; g + 1 < pop->groups.size() && e == hipSuccess; ++g) {
-        hipStream_t s2;
-        e = hipStreamCreateWithFlags(&s2, hipStreamNonBlocking);
-        if (e == hipSuccess) pop->side.push_back(s2);
-    }
+    e = add_streams(pop->side, (int)pop->groups.size() - 1);
+    if (e == hipSuccess) e = hipStreamCreateWithFlags(&pop->cap, hipStreamNonBlocking);
     for (size_t g = 0; g < 2 * pop->groups.size() && e == hipSuccess; ++g) {
         hipEvent_t ev;
         e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
@@ -636,7 +671,7 @@ int enqueue_steps(sr_pop *pop, int n_steps, float2 *sc, hipStream_t st) {
                 hipStream_t sq = pop->lane[g] == 0 ? st : pop->side[pop->lane[g] - 1];
                 HIPC(pop, launch_persistent(gr.cfg, pop->phase, pop->d_robots, pop->d_lists + gr.offset, gr.count,
                                             gr.count, pop->pl, pop->xbuf[pop->cur], pop->vbuf[pop->cur],
-                                            sc + t0, cnt, pop->diverged, pop->c, sq));
+                                            sc + t0, cnt, pop->diverged, pop->c, nullptr, nullptr, sq));
             }
         }
         for (int l = 1; l < G; ++l)
@@ -658,53 +693,90 @@ int pop_set_graphs(sr_pop *pop, int32_t enable) {
 }
 
 namespace {
+// Runs f(g, stream) for every side group on its recording lane, the lanes
+// forked from and joined back into the population's stream (which may share a
+// hardware queue with one of them, so it takes none of the work); a single
+// group stays on the population's stream.
+extern "C++" template <class F>
+int on_lanes(sr_pop *pop, F f) {
+    if (pop->groups.size() == 1) return f(0, pop->st);
+    bool used[REC_LANES] = {};
+    for (int l : pop->rec_lane) used[l] = true;
+    HIPC(pop, hipEventRecord(pop->ev[0], pop->st));
+    for (int l = 0; l < REC_LANES; ++l)
+        if (used[l]) HIPC(pop, hipStreamWaitEvent(pop->rec_st[l], pop->ev[0], 0));
+    for (int g : pop->rec_order) {
+        const int rc = f(g, pop->rec_st[pop->rec_lane[g]]);
+        if (rc) return rc;
+    }
+    for (int l = 0; l < REC_LANES; ++l)
+        if (used[l]) {
+            HIPC(pop, hipEventRecord(pop->ev[l], pop->rec_st[l]));
+            HIPC(pop, hipStreamWaitEvent(pop->st, pop->ev[l], 0));
+        }
+    return SR_OK;
+}
+
 // Steps with checkpoints: the time table in sc (n_steps entries), then blocks
-// of steps that end at every checkpoint, each checkpoint copied into the
-// buffers pop_record allocated.
+// of steps that end at every checkpoint, each checkpoint written into the
+// buffers pop_record allocated (persistent form: by the launch that starts
+// there).  Every side group runs its blocks one after another, the groups side
+// by side: a group of few robots leaves most CUs free.
 int recorded_steps(sr_pop *pop, int n_steps, float2 *sc) {
     const double omega_dt = 2.0 * M_PI * (double)pop->p.act_freq * pop->p.dt;
     HIPC(pop, launch_sincos(sc, pop->d_step, n_steps, omega_dt, pop->c.actuation, pop->st));
-    const int K = pop->rec_valid ? pop->ck_every : 0;
+    const int K = pop->ck_every;
+    struct Block {
+        int t, len;
+        int64_t ck;  // checkpoint at its start, -1 for none
+    };
+    std::vector<Block> blocks;
     for (int t = 0; t < n_steps;) {
         const int64_t g = pop->h_step + t;  // step index at the start of this block
-        int len = n_steps - t;
-        if (pop->spl > 0 && len > pop->spl) len = pop->spl;
-        if (K > 0 && pop->rec_valid) {
+        Block b{t, n_steps - t, -1};
+        if (pop->spl > 0 && b.len > pop->spl) b.len = pop->spl;
+        if (pop->rec_valid) {
             if (g % K == 0) {
-                const int64_t cidx = g / K;
-                if (cidx < pop->ck_cap) {
-                    const size_t off = (size_t)cidx * pop->total_slots;
-                    HIPC(pop, hipMemcpyAsync(pop->ck_x + off, pop->xbuf[pop->cur], sizeof(float4) * pop->total_slots,
-                                             hipMemcpyDeviceToDevice, pop->st));
-                    HIPC(pop, hipMemcpyAsync(pop->ck_v + off, pop->vbuf[pop->cur], sizeof(float4) * pop->total_slots,
-                                             hipMemcpyDeviceToDevice, pop->st));
-                } else {
-                    pop->rec_valid = false;  // past the recorded horizon
-                }
+                if (g / K < pop->ck_cap) b.ck = g / K;
+                else pop->rec_valid = false;  // past the recorded horizon
             }
-            const int to_ck = (int)(K - g % K);
-            if (len > to_ck) len = to_ck;
+            b.len = std::min(b.len, (int)(K - g % K));
         }
-        if (pop->mode == SR_STEP_PLAIN) {
-            for (int q = 0; q < len; ++q) {
+        blocks.push_back(b);
+        t += b.len;
+    }
+    const size_t S = pop->total_slots;
+    if (pop->mode == SR_STEP_PLAIN) {
+        for (const Block &bl : blocks) {
+            if (bl.ck >= 0) {
+                HIPC(pop, hipMemcpyAsync(pop->ck_x + S * bl.ck, pop->xbuf[pop->cur], sizeof(float4) * S,
+                                         hipMemcpyDeviceToDevice, pop->st));
+                HIPC(pop, hipMemcpyAsync(pop->ck_v + S * bl.ck, pop->vbuf[pop->cur], sizeof(float4) * S,
+                                         hipMemcpyDeviceToDevice, pop->st));
+            }
+            for (int q = 0; q < bl.len; ++q) {
                 const int a = pop->cur, b = 1 - pop->cur;
-                HIPC(pop, launch_plain_step(pop->d_robots, pop->total_slots, pop->ix, pop->pl,
-                                            pop->xbuf[a], pop->vbuf[a], pop->xbuf[b], pop->vbuf[b], sc, t + q,
-                                            pop->phase, pop->diverged, pop->slot_robot, pop->c, pop->st));
+                HIPC(pop, launch_plain_step(pop->d_robots, pop->total_slots, pop->ix, pop->pl, pop->xbuf[a],
+                                            pop->vbuf[a], pop->xbuf[b], pop->vbuf[b], sc, bl.t + q, pop->phase,
+                                            pop->diverged, pop->slot_robot, pop->c, pop->st));
                 pop->cur = b;
             }
-        } else {
-            for (const auto &gr : pop->groups) {
-                HIPC(pop, launch_persistent(gr.cfg, pop->phase, pop->d_robots, pop->d_lists + gr.offset, gr.count,
-                                            gr.count, pop->pl, pop->xbuf[pop->cur], pop->vbuf[pop->cur], sc + t,
-                                            len, pop->diverged, pop->c, pop->st));
-            }
         }
-        t += len;
-    }
-    if (pop->mode == SR_STEP_PLAIN)
         HIPC(pop, launch_check_div(pop->d_robots, pop->R, pop->xbuf[pop->cur], pop->vbuf[pop->cur], pop->diverged,
                                    pop->c.lim, pop->st));
+    } else {
+        const int rc = on_lanes(pop, [&](int g, hipStream_t st) -> int {
+            const SideGroup &gr = pop->groups[g];
+            for (const Block &bl : blocks)
+                HIPC(pop, launch_persistent(gr.cfg, pop->phase, pop->d_robots, pop->d_lists + gr.offset, gr.count,
+                                            gr.count, pop->pl, pop->xbuf[pop->cur], pop->vbuf[pop->cur], sc + bl.t,
+                                            bl.len, pop->diverged, pop->c,
+                                            bl.ck >= 0 ? pop->ck_x + S * bl.ck : nullptr,
+                                            bl.ck >= 0 ? pop->ck_v + S * bl.ck : nullptr, st));
+            return SR_OK;
+        });
+        if (rc) return rc;
+    }
     HIPC(pop, launch_advance(pop->d_step, n_steps, pop->st));
     pop->h_step += n_steps;
     return SR_OK;
@@ -897,6 +969,9 @@ int pop_record(sr_pop *pop, int32_t checkpoint_every, int32_t max_steps) {
     hipError_t e = dalloc(&pop->ck_x, (size_t)cap * pop->total_slots);
     if (e == hipSuccess) e = dalloc(&pop->ck_v, (size_t)cap * pop->total_slots);
     if (e != hipSuccess) return set_err(SR_ENOMEM, "checkpoint storage: %s", hipGetErrorString(e));
+    // created one after another, so that the runtime deals them to different hardware queues
+    e = add_streams(pop->rec_st, REC_LANES);
+    if (e != hipSuccess) return fail_hip(pop, e, "recording streams");
     pop->ck_every = checkpoint_every;
     pop->ck_cap = cap;
     pop->rec_valid = pop->built && pop->h_step == 0;
@@ -911,8 +986,7 @@ int ensure_adj_scratch(sr_pop *pop, int K) {
     for (void *p : old)
         if (p) HIPC(pop, hipFree(p));
     for (int b = 0; b < NSET; ++b) {
-        void *seg[] = {pop->rec_x[b], pop->rec_v[b], pop->rec_u[b], pop->rec_l[b], pop->tmp_x[b], pop->tmp_v[b],
-                       pop->sc_seg[b]};
+        void *seg[] = {pop->rec_x[b], pop->rec_v[b], pop->rec_u[b], pop->rec_l[b]};
         for (void *p : seg)
             if (p) HIPC(pop, hipFree(p));
         pop->rec_u[b] = pop->rec_l[b] = nullptr;
@@ -928,9 +1002,6 @@ int ensure_adj_scratch(sr_pop *pop, int K) {
         if (e == hipSuccess) e = dalloc(&pop->rec_v[b], S * K);
         if (e == hipSuccess && vel) e = dalloc(&pop->rec_u[b], S * K);
         if (e == hipSuccess && split) e = dalloc(&pop->rec_l[b], S * K);
-        if (e == hipSuccess) e = dalloc(&pop->tmp_x[b], S);
-        if (e == hipSuccess) e = dalloc(&pop->tmp_v[b], S);
-        if (e == hipSuccess) e = dalloc(&pop->sc_seg[b], (size_t)K);
     }
     if (e == hipSuccess) e = dalloc(&pop->lx, S);
     if (e == hipSuccess) e = dalloc(&pop->lv, S);
@@ -939,10 +1010,11 @@ int ensure_adj_scratch(sr_pop *pop, int K) {
     if (e == hipSuccess) e = dalloc(&pop->gc, S * NDIR);
     if (e == hipSuccess && vel) e = dalloc(&pop->gd, S * NDIR);
     if (e == hipSuccess) e = dalloc(&pop->dJdw, (size_t)pop->total_vox);
-    if (e == hipSuccess && !pop->adj_st) e = hipStreamCreateWithFlags(&pop->adj_st, hipStreamNonBlocking);
-    if (e == hipSuccess && !pop->adj_gst) e = hipStreamCreateWithFlags(&pop->adj_gst, hipStreamNonBlocking);
-    for (auto &ev : pop->adj_ev)
-        if (e == hipSuccess && !ev) e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
+    while (e == hipSuccess && pop->adj_ev.size() < 1 + 3 * NSET * pop->groups.size()) {
+        hipEvent_t ev;
+        e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
+        if (e == hipSuccess) pop->adj_ev.push_back(ev);
+    }
     if (e != hipSuccess) {
         pop->rec_cap = 0;
         return set_err(SR_ENOMEM, "adjoint scratch: %s", hipGetErrorString(e));
@@ -968,65 +1040,89 @@ int pop_backward(sr_pop *pop, const float *dJ_dfitness, float *g_k, float *g_a, 
                               pop->gk, pop->gs, pop->gc, pop->gd, pop->st));
     const int64_t T = pop->h_step;
     const int nseg = (int)((T + K - 1) / K);
-    // Segments are reversed last to first on the population's stream.  The
-    // recomputation (checkpoint -> recorded states) of the segment before runs
-    // meanwhile on adj_st into the other buffer set, so a population too small
-    // to fill the GPU overlaps the two; for the sides whose adjoint is split,
-    // the gradient passes of a segment run on adj_gst while the next segment is
-    // reversed (they read only that segment's buffers and the gradient sums,
-    // which the reversal does not touch).  Events order every buffer reuse.
+    if (T > pop->adj_sc_cap) {
+        HIPC(pop, hipStreamSynchronize(pop->st));
+        if (pop->adj_sc) HIPC(pop, hipFree(pop->adj_sc));
+        pop->adj_sc = nullptr;
+        pop->adj_sc_cap = 0;
+        if (dalloc(&pop->adj_sc, (size_t)T) != hipSuccess) return set_err(SR_ENOMEM, "adjoint time table");
+        pop->adj_sc_cap = (int)T;
+    }
+    HIPC(pop, launch_sincos_at(pop->adj_sc, 0, (int)T, omega_dt, pop->c.actuation, pop->st));
+    // Segments are reversed last to first, each side group on its recording
+    // lane.  A segment's states are recomputed from its checkpoint first: with
+    // one or two groups on a stream of their own, one segment ahead into another
+    // buffer set, so that a population too small to fill the GPU overlaps the
+    // two; with more groups on the group's lane, where the other lanes fill the
+    // GPU.  For the sides whose adjoint is split, the gradient passes of a
+    // segment follow on another stream while the next segment is reversed (they
+    // read only that segment's buffers and the gradient sums, which the reversal
+    // does not touch); they are enqueued one segment late, so that a lane that
+    // carries them does not wait for the longest group.  Events per group order
+    // every buffer reuse.
     const bool vel = pop->c.dash || pop->c.gdamp;
-    bool split = false;
-    for (const auto &g : pop->groups) split = split || adjoint_is_split(g.n, vel);
-    hipEvent_t ev_start = pop->adj_ev[0], *ev_rec = pop->adj_ev + 1, *ev_rev = pop->adj_ev + 1 + NSET,
-               *ev_grd = pop->adj_ev + 1 + 2 * NSET;
-    hipEvent_t *ev_free = split ? ev_grd : ev_rev;  // buffer set b's last readers are done
-    HIPC(pop, hipEventRecord(ev_start, pop->st));
-    HIPC(pop, hipStreamWaitEvent(pop->adj_st, ev_start, 0));
-    auto recompute = [&](int seg) -> int {
+    const int G = (int)pop->groups.size();
+    auto split = [&](int g) { return adjoint_is_split(pop->groups[g].n, vel); };
+    auto event = [&](int what, int g, int b) { return pop->adj_ev[1 + (what * G + g) * NSET + b]; };
+    enum { RECORDED = 0, REVERSED = 1, SUMMED = 2 };
+    auto done = [&](int g, int b) { return event(split(g) ? SUMMED : REVERSED, g, b); };  // set b's last reader
+    auto lane = [&](int g) { return pop->rec_st[pop->rec_lane[g]]; };
+    const bool ahead = G <= 2;  // recomputation on lane G, gradient passes on the one after
+    hipStream_t sum_st = pop->rec_st[ahead ? G + 1 : REC_LANES - 1];
+    auto steps = [&](int seg) { return (int)std::min<int64_t>(K, T - (int64_t)seg * K); };
+    HIPC(pop, hipEventRecord(pop->adj_ev[0], pop->st));
+    for (auto st : pop->rec_st) HIPC(pop, hipStreamWaitEvent(st, pop->adj_ev[0], 0));
+    auto recompute = [&](int seg, int g, hipStream_t st) -> int {
+        const SideGroup &gr = pop->groups[g];
         const int b = seg % NSET;
-        const int64_t s0 = (int64_t)seg * K;
-        const int len = (int)((T - s0) < K ? (T - s0) : K);
         const size_t off = (size_t)seg * pop->total_slots;
-        // buffer set b was last read by the reversal (and gradient passes) of segment seg + NSET
-        if (seg + NSET < nseg) HIPC(pop, hipStreamWaitEvent(pop->adj_st, ev_free[b], 0));
-        HIPC(pop, hipMemcpyAsync(pop->tmp_x[b], pop->ck_x + off, sizeof(float4) * pop->total_slots,
-                                 hipMemcpyDeviceToDevice, pop->adj_st));
-        HIPC(pop, hipMemcpyAsync(pop->tmp_v[b], pop->ck_v + off, sizeof(float4) * pop->total_slots,
-                                 hipMemcpyDeviceToDevice, pop->adj_st));
-        HIPC(pop, launch_sincos_at(pop->sc_seg[b], s0, len, omega_dt, pop->c.actuation, pop->adj_st));
-        for (const auto &gr : pop->groups)
-            HIPC(pop, launch_record(gr.n, pop->phase, pop->d_robots, pop->d_lists + gr.offset, gr.count, pop->pl,
-                                    pop->tmp_x[b], pop->tmp_v[b], pop->sc_seg[b], len, pop->diverged, pop->c,
-                                    pop->rec_x[b], pop->rec_v[b], pop->rec_u[b], pop->adj_st));
-        HIPC(pop, hipEventRecord(ev_rec[b], pop->adj_st));
+        // buffer set b was last read by the reversal (and gradient pass) of segment seg + NSET
+        if (seg + NSET < nseg) HIPC(pop, hipStreamWaitEvent(st, done(g, b), 0));
+        HIPC(pop, launch_record(gr.n, pop->phase, pop->d_robots, pop->d_lists + gr.offset, gr.count, pop->pl,
+                                pop->ck_x + off, pop->ck_v + off, pop->adj_sc + (int64_t)seg * K, steps(seg),
+                                pop->diverged, pop->c, pop->rec_x[b], pop->rec_v[b], pop->rec_u[b], st));
+        HIPC(pop, hipEventRecord(event(RECORDED, g, b), st));
         return SR_OK;
     };
-    if (nseg > 0 && (rc = recompute(nseg - 1))) return rc;
+    auto recompute_ahead = [&](int seg) -> int {
+        for (int g : pop->rec_order)
+            if (ahead && (rc = recompute(seg, g, pop->rec_st[G]))) return rc;
+        return SR_OK;
+    };
+    auto sums = [&](int seg) -> int {
+        const int b = seg % NSET;
+        for (int g : pop->rec_order) {
+            if (!split(g)) continue;
+            const SideGroup &gr = pop->groups[g];
+            HIPC(pop, hipStreamWaitEvent(sum_st, event(REVERSED, g, b), 0));
+            HIPC(pop, launch_adj_grad(gr.n, pop->phase, pop->d_robots, pop->d_lists + gr.offset, gr.count, pop->pl,
+                                      pop->x0, pop->rec_x[b], pop->rec_u[b], pop->rec_l[b], steps(seg),
+                                      pop->adj_sc + (int64_t)seg * K, pop->gk, pop->gs, pop->gc, pop->gd, pop->c,
+                                      sum_st));
+            HIPC(pop, hipEventRecord(event(SUMMED, g, b), sum_st));
+        }
+        return SR_OK;
+    };
+    if (nseg > 0 && (rc = recompute_ahead(nseg - 1))) return rc;
     for (int seg = nseg - 1; seg >= 0; --seg) {
         const int b = seg % NSET;
-        const int64_t s0 = (int64_t)seg * K;
-        const int len = (int)((T - s0) < K ? (T - s0) : K);
-        if (seg > 0 && (rc = recompute(seg - 1))) return rc;
-        HIPC(pop, hipStreamWaitEvent(pop->st, ev_rec[b], 0));
-        for (const auto &gr : pop->groups)
+        if (seg > 0 && (rc = recompute_ahead(seg - 1))) return rc;
+        for (int g : pop->rec_order) {
+            const SideGroup &gr = pop->groups[g];
+            if (!ahead && (rc = recompute(seg, g, lane(g)))) return rc;
+            HIPC(pop, hipStreamWaitEvent(lane(g), event(RECORDED, g, b), 0));
             HIPC(pop, launch_adjoint(gr.n, pop->phase, pop->d_robots, pop->d_lists + gr.offset, gr.count, pop->pl,
-                                     pop->x0, pop->rec_x[b], pop->rec_v[b], pop->rec_u[b], pop->rec_l[b], len,
-                                     pop->sc_seg[b],
-                                     pop->lx, pop->lv, pop->gk, pop->gs, pop->gc, pop->gd, pop->c, pop->st));
-        HIPC(pop, hipEventRecord(ev_rev[b], pop->st));
-        if (split) {
-            HIPC(pop, hipStreamWaitEvent(pop->adj_gst, ev_rev[b], 0));
-            for (const auto &gr : pop->groups)
-                if (adjoint_is_split(gr.n, vel))
-                    HIPC(pop, launch_adj_grad(gr.n, pop->phase, pop->d_robots, pop->d_lists + gr.offset, gr.count,
-                                              pop->pl, pop->x0, pop->rec_x[b], pop->rec_u[b], pop->rec_l[b], len,
-                                              pop->sc_seg[b], pop->gk, pop->gs, pop->gc, pop->gd, pop->c,
-                                              pop->adj_gst));
-            HIPC(pop, hipEventRecord(ev_grd[b], pop->adj_gst));
+                                     pop->x0, pop->rec_x[b], pop->rec_v[b], pop->rec_u[b], pop->rec_l[b], steps(seg),
+                                     pop->adj_sc + (int64_t)seg * K, pop->lx, pop->lv, pop->gk, pop->gs, pop->gc,
+                                     pop->gd, pop->c, lane(g)));
+            HIPC(pop, hipEventRecord(event(REVERSED, g, b), lane(g)));
         }
+        if (ahead && (rc = sums(seg))) return rc;
+        if (!ahead && seg + 1 < nseg && (rc = sums(seg + 1))) return rc;
     }
-    if (split && nseg > 0) HIPC(pop, hipStreamWaitEvent(pop->st, ev_grd[0], 0));  // segment 0's sums
+    if (nseg > 0 && !ahead && (rc = sums(0))) return rc;
+    if (nseg > 0)
+        for (int g = 0; g < G; ++g) HIPC(pop, hipStreamWaitEvent(pop->st, done(g, 0), 0));  // segment 0's sums
     HIPC(pop, launch_adj_springs(pop->d_robots, pop->total_slots, pop->slot_robot, pop->ix, pop->d_spring_off, pop->pl,
                                  pop->p.voxel_len, pop->gk, pop->gs, pop->gc, g_k, g_a, g_phi, pop->st));
     if (g_genome)

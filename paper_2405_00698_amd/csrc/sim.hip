@@ -187,9 +187,12 @@ struct PArgs {
     int n_steps;
     uint8_t *diverged;
     SimConst c;
+    // checkpoint of the state at the launch's start (null: none)
+    float4 *ck_x, *ck_v;
     // recording form: per step the positions x_n and the pre-friction velocity v'_n
     // of every slot, at rec_x[n_steps * slot_base + t * slots + s]; rec_u (when
-    // not null) the velocity v_n at the start of the step
+    // not null) the velocity v_n at the start of the step.  Its end state is not
+    // stored: x and v are the checkpoint it starts from.
     float4 *rec_x, *rec_v, *rec_u;
 };
 
@@ -568,6 +571,10 @@ __global__ __launch_bounds__(BS) void k_persist(PArgs A) {
             const float4 X = A.x[base + sc_];
             const float4 V = A.v[base + sc_];
             if (live) {
+                if (!REC && A.ck_x) {
+                    A.ck_x[base + s] = X;
+                    A.ck_v[base + s] = V;
+                }
                 xb0[PAD + s] = X;
                 if constexpr (!SBX) xb1[PAD + s] = X;
                 if constexpr (DASH) vb[PAD + s] = V;
@@ -1039,8 +1046,10 @@ __global__ __launch_bounds__(BS) void k_persist(PArgs A) {
         for (int k = 0; k < NPT; ++k) {
             const int s = sk[k];
             if (pres[k]) {
-                A.x[base + s] = make_float4(xr[k].x, xr[k].y, xr[k].z, 1.f);
-                A.v[base + s] = make_float4(vr[k].x, vr[k].y, vr[k].z, 0.f);
+                if (!REC) {
+                    A.x[base + s] = make_float4(xr[k].x, xr[k].y, xr[k].z, 1.f);
+                    A.v[base + s] = make_float4(vr[k].x, vr[k].y, vr[k].z, 0.f);
+                }
                 mybad |= node_bad(xr[k], vr[k], lim);
             }
         }
@@ -1390,7 +1399,7 @@ int persist_default_block(int n, bool dash, bool vox, int *variant) {
 
 hipError_t launch_persistent(const PersistCfg &cfg, bool phase, const RobotInfo *robots, const int32_t *list, int count,
                              int grid, Planes pl, float4 *x, float4 *v, const float2 *sc, int n_steps,
-                             uint8_t *diverged, SimConst c, hipStream_t st) {
+                             uint8_t *diverged, SimConst c, float4 *ck_x, float4 *ck_v, hipStream_t st) {
     const PersistEntry *e = find_persist(cfg);
     if (!e) return hipErrorInvalidConfiguration;
     PArgs A;
@@ -1404,6 +1413,8 @@ hipError_t launch_persistent(const PersistCfg &cfg, bool phase, const RobotInfo 
     A.n_steps = n_steps;
     A.diverged = diverged;
     A.c = c;
+    A.ck_x = ck_x;
+    A.ck_v = ck_v;
     A.rec_x = nullptr;
     A.rec_v = nullptr;
     A.rec_u = nullptr;
@@ -1413,8 +1424,8 @@ hipError_t launch_persistent(const PersistCfg &cfg, bool phase, const RobotInfo 
 }
 
 hipError_t launch_record(int n, bool phase, const RobotInfo *robots, const int32_t *list, int count, Planes pl,
-                         float4 *x, float4 *v, const float2 *sc, int n_steps, uint8_t *diverged, SimConst c,
-                         float4 *rec_x, float4 *rec_v, float4 *rec_u, hipStream_t st) {
+                         const float4 *x, const float4 *v, const float2 *sc, int n_steps, uint8_t *diverged,
+                         SimConst c, float4 *rec_x, float4 *rec_v, float4 *rec_u, hipStream_t st) {
     // the spring-dashpot model records with the dashpot kernels (the same bits
     // as its production kernels)
     const PersistEntry *e = nullptr;
@@ -1431,12 +1442,14 @@ hipError_t launch_record(int n, bool phase, const RobotInfo *robots, const int32
     A.list = list;
     A.count = count;
     A.pl = pl;
-    A.x = x;
-    A.v = v;
+    A.x = const_cast<float4 *>(x);  // only read by the recording form
+    A.v = const_cast<float4 *>(v);
     A.sc = sc;
     A.n_steps = n_steps;
     A.diverged = diverged;
     A.c = c;
+    A.ck_x = nullptr;
+    A.ck_v = nullptr;
     A.rec_x = rec_x;
     A.rec_v = rec_v;
     A.rec_u = rec_u;
