@@ -179,7 +179,8 @@ int pop_set_graphs(sr_pop *pop, int32_t enable);
 /* Picks the persistent kernel for robots of side n: block threads per
  * workgroup and variant, a sum of
  *   0 recompute every spring force at both ends, 1 exchange spring
- *     coefficients through LDS, 2 exchange in two direction chunks;
+ *     coefficients through LDS, 2 exchange in two direction chunks, 3 in
+ *     chunks of three directions;
  *   +4 bounds the LDS loads in flight to save registers;
  *   +8 reads positions with 12-byte instead of 16-byte LDS loads;
  *   +16 marks the kernels with spring dashpots, which also share velocities

@@ -120,7 +120,8 @@ hipError_t launch_sincos_at(float2 *sc, int64_t step0, int n, double omega_dt, i
 
 // recording forward for the adjoint: x_n and the pre-friction velocity v'_n of
 // every step, and (rec_u not null: dashpots or a damped ground) v_n as well
-hipError_t launch_record(int n, bool phase, const RobotInfo *robots, const int32_t *list, int count, Planes pl,
+// (vox: the voxel terms match the spring planes)
+hipError_t launch_record(int n, bool phase, bool vox, const RobotInfo *robots, const int32_t *list, int count, Planes pl,
                          const float4 *x, const float4 *v, const float2 *sc, int n_steps, uint8_t *diverged, SimConst c,
                          float4 *rec_x, float4 *rec_v, float4 *rec_u, hipStream_t st);
 // reverse step over one recorded segment; for a side whose adjoint is split
@@ -159,7 +160,7 @@ hipError_t launch_check_div(const RobotInfo *robots, int R, const float4 *x, con
 
 // persistent LDS-resident kernel for robots of side n; `list` holds the robot
 // ids to step (all of side n); ck_x, ck_v (or null) take the state it starts from.  variant: 0 recompute, 1 exchange, 2 exchange
-// in two direction chunks (+4 fences, +8 12-byte loads, +16 spring dashpots,
+// in two direction chunks, 3 in chunks of three directions (+4 fences, +8 12-byte loads, +16 spring dashpots,
 // +32/+64 parameters rebuilt from voxels, +128 one position buffer).
 struct PersistCfg {
     int n, block, variant;

@@ -115,7 +115,7 @@ struct sr_pop {
     uint8_t *q_cls = nullptr;
     int32_t *vox_robot = nullptr;
     // adjoint: checkpoints of (x, v) at steps 0, K, 2K, ... since the build
-    int ck_every = 0, ck_cap = 0;
+    int ck_every = 0, ck_cap = 0, ck_alloc = 0;
     bool rec_valid = false;
     float4 *ck_x = nullptr, *ck_v = nullptr;
     // adjoint scratch (grown on demand)
@@ -486,7 +486,6 @@ int pop_create(const sr_sim_params *params, int32_t n_robots, const int32_t *gri
     // private streams (default priority) for capturing step graphs: one per
     // extra size group, so the groups become parallel branches of one graph
     e = add_streams(pop->side, (int)pop->groups.size() - 1);
-    if (e == hipSuccess) e = hipStreamCreateWithFlags(&pop->cap, hipStreamNonBlocking);
     for (size_t g = 0; g < 2 * pop->groups.size() && e == hipSuccess; ++g) {
         hipEvent_t ev;
         e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
@@ -800,6 +799,9 @@ int pop_step(sr_pop *pop, int32_t n_steps) {
         auto it = pop->graphs.find(key);
         const int cur0 = pop->cur;
         if (it == pop->graphs.end()) {
+            // made here, not with the population: a recording one needs the
+            // device's few hardware queues for its lanes
+            if (!pop->cap) HIPC(pop, hipStreamCreateWithFlags(&pop->cap, hipStreamNonBlocking));
             HIPC(pop, hipStreamBeginCapture(pop->cap, hipStreamCaptureModeThreadLocal));
             rc = enqueue_steps(pop, n_steps, pop->sc, pop->cap);
             hipGraph_t graph = nullptr;
@@ -957,18 +959,29 @@ int pop_reset(sr_pop *pop) {
 int pop_record(sr_pop *pop, int32_t checkpoint_every, int32_t max_steps) {
     CHECK_POP(pop);
     if (checkpoint_every < 0 || max_steps < 0) return set_err(SR_EINVAL, "negative checkpoint interval or horizon");
-    if (pop->ck_x) HIPC(pop, hipStreamSynchronize(pop->st));
-    if (pop->ck_x) HIPC(pop, hipFree(pop->ck_x));
-    if (pop->ck_v) HIPC(pop, hipFree(pop->ck_v));
-    pop->ck_x = pop->ck_v = nullptr;
     pop->ck_every = 0;
-    pop->ck_cap = 0;
     pop->rec_valid = false;
-    if (checkpoint_every == 0) return SR_OK;
-    const int cap = max_steps / checkpoint_every + 1;
-    hipError_t e = dalloc(&pop->ck_x, (size_t)cap * pop->total_slots);
-    if (e == hipSuccess) e = dalloc(&pop->ck_v, (size_t)cap * pop->total_slots);
-    if (e != hipSuccess) return set_err(SR_ENOMEM, "checkpoint storage: %s", hipGetErrorString(e));
+    const int cap = checkpoint_every > 0 ? max_steps / checkpoint_every + 1 : 0;
+    if (cap == 0 || cap > pop->ck_alloc) {
+        if (pop->ck_x) HIPC(pop, hipStreamSynchronize(pop->st));
+        if (pop->ck_x) HIPC(pop, hipFree(pop->ck_x));
+        if (pop->ck_v) HIPC(pop, hipFree(pop->ck_v));
+        pop->ck_x = pop->ck_v = nullptr;
+        pop->ck_alloc = 0;
+    }
+    pop->ck_cap = 0;
+    if (cap == 0) return SR_OK;
+    hipError_t e = hipSuccess;
+    if (!pop->ck_x) {
+        e = dalloc(&pop->ck_x, (size_t)cap * pop->total_slots);
+        if (e == hipSuccess) e = dalloc(&pop->ck_v, (size_t)cap * pop->total_slots);
+        if (e != hipSuccess) {
+            if (pop->ck_x) (void)hipFree(pop->ck_x);
+            pop->ck_x = nullptr;
+            return set_err(SR_ENOMEM, "checkpoint storage: %s", hipGetErrorString(e));
+        }
+        pop->ck_alloc = cap;
+    }
     // created one after another, so that the runtime deals them to different hardware queues
     e = add_streams(pop->rec_st, REC_LANES);
     if (e != hipSuccess) return fail_hip(pop, e, "recording streams");
@@ -1078,7 +1091,7 @@ int pop_backward(sr_pop *pop, const float *dJ_dfitness, float *g_k, float *g_a, 
         const size_t off = (size_t)seg * pop->total_slots;
         // buffer set b was last read by the reversal (and gradient pass) of segment seg + NSET
         if (seg + NSET < nseg) HIPC(pop, hipStreamWaitEvent(st, done(g, b), 0));
-        HIPC(pop, launch_record(gr.n, pop->phase, pop->d_robots, pop->d_lists + gr.offset, gr.count, pop->pl,
+        HIPC(pop, launch_record(gr.n, pop->phase, pop->vox_ok, pop->d_robots, pop->d_lists + gr.offset, gr.count, pop->pl,
                                 pop->ck_x + off, pop->ck_v + off, pop->adj_sc + (int64_t)seg * K, steps(seg),
                                 pop->diverged, pop->c, pop->rec_x[b], pop->rec_v[b], pop->rec_u[b], st));
         HIPC(pop, hipEventRecord(event(RECORDED, g, b), st));

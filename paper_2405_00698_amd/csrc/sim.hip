@@ -1060,6 +1060,213 @@ __global__ __launch_bounds__(BS) void k_persist(PArgs A) {
     }
 }
 
+// ---------------------------------------------------------------- dashpots at the largest side
+// Step kernel with spring dashpots for a lattice whose springs' parameters fit
+// neither the registers nor, beside both endpoint states, LDS.  Every parameter
+// is rebuilt from voxel terms (as VOX 2 above, the same bits); the state of a
+// slot is split as (x, y, z, vx) and (vy, vz), 24 B instead of two 16-byte
+// arrays, which leaves room for two sets of three coefficient rows: in one
+// phase a node takes its backward springs of chunk c and forms the forward
+// coefficients of chunk c + 1, so 13 directions cost 5 barriers (+ 2 around the
+// node update) and one chunk's LDS latency hides behind the other's arithmetic.
+// All directions are compile-time constants (nothing is indexed at run time, so
+// nothing lives in scratch).  Bound by VALU issue (about 520 instructions per
+// slot and step, 9 runs of 64 slots per SIMD: 8 us).  Measured at 12^3 with one
+// robot per CU: 31.6 -> 8.0 us a step against the two-chunk form with its
+// parameters spilled to scratch, which stays for populations whose springs were
+// set directly.
+template <int N>
+struct GeoVD {
+    using G = Geo<N>;
+    static constexpr int CD = 3;                        // directions per chunk
+    static constexpr int NCH = (NDIR + CD - 1) / CD;
+    static constexpr size_t LDS = G::XL * (sizeof(float4) + sizeof(float2)) + G::CL * sizeof(float4) +
+                                  2 * CD * G::CL * sizeof(float) + sizeof(int);
+};
+
+template <int N, int BS, bool REC>
+__global__ __launch_bounds__(BS) void k_persist_vd(PArgs A) {
+    using G = Geo<N>;
+    constexpr int SL = G::SL, PAD = G::PAD, XL = G::XL, CL = G::CL;
+    constexpr int CD = GeoVD<N>::CD, NCH = GeoVD<N>::NCH;
+    constexpr int NPT = (SL + BS - 1) / BS;
+    __shared__ float4 pb[XL];      // x, y, z, vx
+    __shared__ float2 qb[XL];      // vy, vz
+    __shared__ float4 vv[CL];      // voxel terms
+    __shared__ float coef[2 * CD * CL];
+    __shared__ int bad;
+    const int tid = threadIdx.x;
+    const SimConst c = A.c;
+    for (int q = blockIdx.x; q < A.count; q += gridDim.x) {
+        const int r = A.list[q];
+        if (A.diverged[r]) continue;
+        const int base = A.robots[r].slot_base;
+        const float lim = c.lim * (N - 1);
+        for (int i = tid; i < 2 * CD * CL; i += BS) coef[i] = 0.f;
+        for (int i = tid; i < PAD; i += BS) {
+            pb[i] = pb[PAD + SL + i] = make_float4(1e4f, 1e4f, 1e4f, 0.f);
+            qb[i] = qb[PAD + SL + i] = make_float2(0.f, 0.f);
+            vv[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+        if (tid == 0) bad = 0;
+        float3 xr[NPT], vr[NPT];
+        bool pres[NPT], wk[NPT];
+#pragma unroll
+        for (int k = 0; k < NPT; ++k) {
+            const int s = tid + k * BS;
+            const bool live = s < SL;
+            const float4 X = A.x[base + (live ? s : 0)], V = A.v[base + (live ? s : 0)];
+            if (live) {
+                if (!REC && A.ck_x) {
+                    A.ck_x[base + s] = X;
+                    A.ck_v[base + s] = V;
+                }
+                pb[PAD + s] = make_float4(X.x, X.y, X.z, V.x);
+                qb[PAD + s] = make_float2(V.y, V.z);
+                vv[PAD + s] = A.pl.vkp[base + s];
+            }
+            xr[k] = make_float3(X.x, X.y, X.z);
+            vr[k] = make_float3(V.x, V.y, V.z);
+            pres[k] = live && X.w != 0.f;
+            // a wave of absent points has no spring: its coefficients stay zero
+            wk[k] = live && __ballot(pres[k] ? 1 : 0) != 0ull;
+        }
+        __syncthreads();
+        float2 sc_next = A.sc[0];
+        for (int t = 0; t < A.n_steps; ++t) {
+            const float2 sct = sc_next;
+            if (t + 1 < A.n_steps) sc_next = A.sc[t + 1];
+            float3 Ff[NPT], Fb[NPT];
+#pragma unroll
+            for (int k = 0; k < NPT; ++k) {
+                Ff[k] = make_float3(0.f, 0.f, 0.f);
+                Fb[k] = make_float3(0.f, 0.f, 0.f);
+            }
+            // forward coefficients of chunk C, into its set of rows
+            auto forward = [&](auto CC) {
+                constexpr int C0 = decltype(CC)::value * CD, C1 = C0 + CD < NDIR ? C0 + CD : NDIR;
+                constexpr int SET = decltype(CC)::value % 2;
+#pragma unroll
+                for (int k = 0; k < NPT; ++k) {
+                    int s = tid + k * BS;
+                    if (!wk[k]) continue;
+                    // the voxel terms never change, but must be re-read every step
+                    __asm__ volatile("" : "+v"(s));
+                    if constexpr (SR_POISON_LDS)
+                        for (int j = 0; j < C1 - C0; ++j) coef[(SET * CD + j) * CL + PAD + s] = __builtin_nanf("");
+                    float4 P[CD];
+                    float2 Q[CD];
+                    float4 Vx[8];
+#pragma unroll
+                    for (int j = 0; j < CD; ++j)
+                        if (C0 + j < C1) {
+                            P[j] = pb[PAD + s + dir_off(C0 + j, N)];
+                            Q[j] = qb[PAD + s + dir_off(C0 + j, N)];
+                        }
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) Vx[i] = vv[PAD + s + vox_off(i, N)];
+#pragma unroll
+                    for (int j = 0; j < CD; ++j) {
+                        if (C0 + j >= C1) continue;
+                        const int d = C0 + j;
+                        const float dx = P[j].x - xr[k].x, dy = P[j].y - xr[k].y, dz = P[j].z - xr[k].z;
+                        float4 sm = Vx[vox_idx(d, 0)];
+#pragma unroll
+                        for (int i = 1; i < vox_cnt(d); ++i) {
+                            const float4 u = Vx[vox_idx(d, i)];
+                            sm.x = add_nf(sm.x, u.x);
+                            sm.y = add_nf(sm.y, u.y);
+                            sm.z = add_nf(sm.z, u.z);
+                            sm.w = add_nf(sm.w, u.w);
+                        }
+                        const float cf = spring_coef_d<true>(
+                            sm.x, sm.x * L0d(c, d), mul_nf(sm.y, L0d(c, d)), mul_nf(sm.z, L0d(c, d)), sct.x, sct.y,
+                            len2(dx, dy, dz), sm.w,
+                            rate(P[j].w - vr[k].x, Q[j].x - vr[k].y, Q[j].y - vr[k].z, dx, dy, dz));
+                        coef[(SET * CD + j) * CL + PAD + s] = cf;
+                        Ff[k].x = fmaf(cf, dx, Ff[k].x);
+                        Ff[k].y = fmaf(cf, dy, Ff[k].y);
+                        Ff[k].z = fmaf(cf, dz, Ff[k].z);
+                    }
+                }
+            };
+            auto backward = [&](auto CC) {
+                constexpr int C0 = decltype(CC)::value * CD, C1 = C0 + CD < NDIR ? C0 + CD : NDIR;
+                constexpr int SET = decltype(CC)::value % 2;
+#pragma unroll
+                for (int k = 0; k < NPT; ++k) {
+                    const int s = tid + k * BS;
+                    if (!wk[k]) continue;
+                    float4 P[CD];
+                    float cf[CD];
+#pragma unroll
+                    for (int j = 0; j < CD; ++j)
+                        if (C0 + j < C1) {
+                            P[j] = pb[PAD + s - dir_off(C0 + j, N)];
+                            cf[j] = coef[(SET * CD + j) * CL + PAD + s - dir_off(C0 + j, N)];
+                        }
+#pragma unroll
+                    for (int j = 0; j < CD; ++j) {
+                        if (C0 + j >= C1) continue;
+                        keep_w(P[j].w);
+                        Fb[k].x = fmaf(cf[j], P[j].x - xr[k].x, Fb[k].x);
+                        Fb[k].y = fmaf(cf[j], P[j].y - xr[k].y, Fb[k].y);
+                        Fb[k].z = fmaf(cf[j], P[j].z - xr[k].z, Fb[k].z);
+                    }
+                }
+            };
+            static_assert(NCH == 5, "the phases below");
+            forward(IC<0>{});
+            __syncthreads();
+            backward(IC<0>{});
+            forward(IC<1>{});
+            __syncthreads();
+            backward(IC<1>{});
+            forward(IC<2>{});
+            __syncthreads();
+            backward(IC<2>{});
+            forward(IC<3>{});
+            __syncthreads();
+            backward(IC<3>{});
+            forward(IC<4>{});
+            __syncthreads();
+            backward(IC<4>{});
+            __syncthreads();  // every read of the step is done before the update
+#pragma unroll
+            for (int k = 0; k < NPT; ++k) {
+                const int s = tid + k * BS;
+                if (!pres[k]) continue;
+                const size_t at = (size_t)A.n_steps * base + (size_t)t * SL + s;
+                float3 vp;
+                if (REC) {
+                    A.rec_x[at] = make_float4(xr[k].x, xr[k].y, xr[k].z, 1.f);
+                    A.rec_u[at] = make_float4(vr[k].x, vr[k].y, vr[k].z, 0.f);
+                }
+                integrate_node(c, xr[k], vr[k], Ff[k], Fb[k], REC ? &vp : nullptr);
+                if (REC) A.rec_v[at] = make_float4(vp.x, vp.y, vp.z, 0.f);
+                pb[PAD + s] = make_float4(xr[k].x, xr[k].y, xr[k].z, vr[k].x);
+                qb[PAD + s] = make_float2(vr[k].y, vr[k].z);
+            }
+            __syncthreads();
+        }
+        bool mybad = false;
+#pragma unroll
+        for (int k = 0; k < NPT; ++k) {
+            const int s = tid + k * BS;
+            if (!pres[k]) continue;
+            if (!REC) {
+                A.x[base + s] = make_float4(xr[k].x, xr[k].y, xr[k].z, 1.f);
+                A.v[base + s] = make_float4(vr[k].x, vr[k].y, vr[k].z, 0.f);
+            }
+            mybad |= node_bad(xr[k], vr[k], lim);
+        }
+        if (mybad) bad = 1;
+        __syncthreads();
+        if (tid == 0 && bad) A.diverged[r] = 1;
+        __syncthreads();
+    }
+}
+
 // ---------------------------------------------------------------- fitness
 __global__ __launch_bounds__(256) void k_fitness(const RobotInfo *robots, const float4 *x, const float4 *x0,
                                                  const uint8_t *diverged, float *fit) {
@@ -1164,7 +1371,7 @@ struct PersistEntry {
 };
 
 // Variant codes (the sum documented at pop_set_persist_variant): exchange
-// variant (0, 1, 2); + 4 scheduling fences bound the LDS loads in flight; + 8
+// variant (0, 1, 2, 3); + 4 scheduling fences bound the LDS loads in flight; + 8
 // 12-byte instead of 16-byte position loads; + 16 spring-dashpot kernels;
 // + 32 * VOX spring parameters of the face and body diagonals (VOX 1) or of
 // every direction (VOX 2) rebuilt from voxels each step; + 128 one position
@@ -1252,6 +1459,13 @@ constexpr size_t lds_ok() {
             k_persist<NN + 1, BS, 2, false, true, false, true, true, 0, true>,                                   \
             lds_ok<lds_bytes<NN + 1, BS, 2, true, 0, true>()>()                                                  \
     }
+// chunks of three directions in two alternating sets of rows, parameters from
+// voxels, one buffer (12^3)
+#define SR_PDV(NN, BS)                                                                                       \
+    {                                                                                                        \
+        NN, BS, 3 + 16 + 64 + 128, k_persist_vd<NN + 1, BS, false>, k_persist_vd<NN + 1, BS, false>,           \
+            lds_ok<GeoVD<NN + 1>::LDS>()                                                                     \
+    }
 // dashpot kernels carry the phase plane always (with a zero plane the results
 // are the same bits as without it); SR_PDF / SR_PDVF software-pipeline their
 // position and velocity reads
@@ -1301,7 +1515,7 @@ const PersistEntry kPersist[] = {
     SR_PD(1, 64, 1),            SR_PD(2, 64, 1),            SR_PD(3, 64, 1),
     SR_PDF(4, 128, 3, 3),       SR_PDF(5, 256, 3, 3),       SR_PDF(6, 384, 3, 3),       SR_PDF(7, 512, 3, 3),
     SR_PDF(8, 768, 3, 3),       SR_PDF(9, 1024, 3, 3),      SR_PDT(10, 768, 2, 2, 1),   SR_PDT(11, 1024, 1, 1, 1),
-    SR_PDC(12, 768),            SR_PDVF(10, 704, 2, 1, 3, 3),
+    SR_PDV(12, 768),            SR_PDC(12, 768),            SR_PDVF(10, 704, 2, 1, 3, 3),
     SR_PD(8, 768, 1),
 };
 
@@ -1355,6 +1569,7 @@ const PersistEntry kRecD[] = {
     SR_RECD(1, 64, 1),         SR_RECD(2, 64, 1),          SR_RECD(3, 64, 1),         SR_RECDF(4, 128, 3, 3),
     SR_RECDF(5, 256, 3, 3),    SR_RECDF(6, 384, 3, 3),     SR_RECDF(7, 512, 3, 3),    SR_RECDF(8, 768, 3, 3),
     SR_RECDF(9, 1024, 3, 3),   SR_RECDT(10, 768, 2, 2, 1), SR_RECDT(11, 1024, 1, 1, 1), SR_RECDC(12, 768),
+    {12, 768, 3 + 16 + 64 + 128, k_persist_vd<13, 768, true>, k_persist_vd<13, 768, true>, 0},
 };
 
 const PersistEntry *find_persist(const PersistCfg &cfg) {
@@ -1423,15 +1638,16 @@ hipError_t launch_persistent(const PersistCfg &cfg, bool phase, const RobotInfo 
     return hipGetLastError();
 }
 
-hipError_t launch_record(int n, bool phase, const RobotInfo *robots, const int32_t *list, int count, Planes pl,
+hipError_t launch_record(int n, bool phase, bool vox, const RobotInfo *robots, const int32_t *list, int count, Planes pl,
                          const float4 *x, const float4 *v, const float2 *sc, int n_steps, uint8_t *diverged,
                          SimConst c, float4 *rec_x, float4 *rec_v, float4 *rec_u, hipStream_t st) {
     // the spring-dashpot model records with the dashpot kernels (the same bits
     // as its production kernels)
     const PersistEntry *e = nullptr;
     if (c.dash) {
+        // the last entry of the side whose parameters match the planes
         for (const auto &q : kRecD)
-            if (q.n == n) e = &q;
+            if (q.n == n && (vox || !(q.variant & 96))) e = &q;
     } else {
         for (const auto &q : kRec)
             if (q.n == n) e = &q;
