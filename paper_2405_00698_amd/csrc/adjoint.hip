@@ -812,146 +812,217 @@ __global__ void k_adj_dw(DwArgs A) {
 
 // Genome gradient: for each voxel with dJ/dw != 0, recompute the FP32 forward
 // (encoding, two tanh layers, sigmoid head), g5 = dJ/dw w (1 - w), then back
-// through W3 row 5, W2 and W1.  One workgroup per robot; weight gradients are
-// accumulated in registers over tiles of 64 voxels staged in LDS.
+// through W3 row 5, W2 and W1.  One workgroup of 8 waves per robot takes tiles
+// of 128 voxels: each wave first runs 16 of them through the network and back on
+// v_mfma_f32_16x16x4_f32 (whose accumulation is an FMA chain in ascending k, so
+// with the bias as the first C this is the scalar loop's arithmetic; layout as
+// in the FP32 genome query: register b of lane quarter kq holds feature 4 b + kq
+// of voxel `col`), and leaves the encodings, h1 and both layers' deltas in LDS;
+// then the waves add the tile's outer products, again as matrix products with
+// the voxels as k in ascending order, wave w the row block w / 2 and two column
+// blocks of both weight gradients, which stay in registers to the end.  Bias and
+// head sums are trees over the 16 voxels of a wave.
+// LDS rows of 72 floats: a wave's writes (16 voxels x 4 features) and its
+// fragment reads (4 voxels x 16 features) meet each bank at most twice.
+// Bound by the tanh and sin/cos (VALU) and the matrix instructions in turn, about
+// 17k cycles a tile.  Measured against one thread per voxel quarter with FMA
+// loops over LDS, 30 uneven robots: 1274 -> 439 us (the 12^3 robots' 14 tiles in a row).
 constexpr int OFF_W1 = 0, OFF_B1 = 4096, OFF_W2 = 4160, OFF_B2 = 8256, OFF_W3 = 8320, OFF_B3 = 8704;
+constexpr int MBT = 512, MBV = 16 * (MBT / 64), MROW = 72;
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-__global__ __launch_bounds__(256) void k_mlp_backward(const RobotInfo *robots, const float *genomes, const float *B,
+// sum over the 16 lanes of a lane quarter, on every one of them (swaps within a
+// quad, across the half row, across the row)
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float sum16(float v) {
+    v += dpp<0xB1>(v);
+    v += dpp<0x4E>(v);
+    v += dpp<0x141>(v);
+    v += dpp<0x140>(v);
+    return v;
+}
+
+__global__ __launch_bounds__(MBT) void k_mlp_backward(const RobotInfo *robots, const float *genomes, const float *B,
                                                       const float *dJdw, float *g_gen) {
-    __shared__ float W1[64 * 64], W2[64 * 64], w3[64], b1[64], b2[64];
-    __shared__ float Bs[96];
-    __shared__ float gam[64][65], h1[64][65], h2[64][65], d2[64][65], d1[64][65];
-    __shared__ float gv5[64];
-    __shared__ float b3s;
+    __shared__ float gamS[MBV * MROW], h1S[MBV * MROW], d1S[MBV * MROW], d2S[MBV * MROW];
+    __shared__ float Bs[96], b1s[64], b2s[64], w3s[64];
     const int r = blockIdx.x;
     const RobotInfo ri = robots[r];
     const int n = ri.n, nv = n * n * n;
     const float *g = genomes + (size_t)r * SR_GENOME_LEN;
     float *out = g_gen + (size_t)r * SR_GENOME_LEN;
-    const int tid = threadIdx.x;
-    for (int q = tid; q < 4096; q += 256) {
-        W1[q] = g[OFF_W1 + q];
-        W2[q] = g[OFF_W2 + q];
-    }
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int col = lane & 15, kq = lane >> 4;
+    const int perm = 4 * (col & 3) + (col >> 2);  // weight row of A row `col` within its block
     if (tid < 64) {
-        w3[tid] = g[OFF_W3 + 5 * 64 + tid];
-        b1[tid] = g[OFF_B1 + tid];
-        b2[tid] = g[OFF_B2 + tid];
+        b1s[tid] = g[OFF_B1 + tid];
+        b2s[tid] = g[OFF_B2 + tid];
+        w3s[tid] = g[OFF_W3 + 5 * 64 + tid];
     }
     if (tid < 96) Bs[tid] = B[tid];
-    if (tid == 0) b3s = g[OFF_B3 + 5];
+    const float b3 = g[OFF_B3 + 5];
+    float w1[4][16];
+#pragma unroll
+    for (int m = 0; m < 4; ++m)
+#pragma unroll
+        for (int b = 0; b < 16; ++b) w1[m][b] = g[OFF_W1 + 64 * (16 * m + perm) + 4 * b + kq];
     __syncthreads();
-    // accumulators: thread owns W1/W2 gradient entries e = tid + 256 m, m < 16
-    float aW1[16], aW2[16];
+    f32x4 a1[2], a2[2];  // gradient blocks of W1 and W2
 #pragma unroll
-    for (int m = 0; m < 16; ++m) {
-        aW1[m] = 0.f;
-        aW2[m] = 0.f;
-    }
-    float aB1 = 0.f, aB2 = 0.f, aW3 = 0.f, aB3 = 0.f;
+    for (int e = 0; e < 2; ++e)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) a1[e][i] = a2[e][i] = 0.f;
+    float s1[16], s2[16], s3[16], s5 = 0.f;  // this wave's sums of d1, d2, g5 h2 (feature 4 b + kq) and g5
+#pragma unroll
+    for (int b = 0; b < 16; ++b) s1[b] = s2[b] = s3[b] = 0.f;
+    const int rb = wave >> 1, cb = 2 * (wave & 1);
     const float inv = 1.0f / (float)n;
-    for (int v0 = 0; v0 < nv; v0 += 64) {
-        // forward for voxel v0 + lane of wave 0..3: each thread does a quarter of one voxel's work
-        const int vl = tid & 63, part = tid >> 6;
-        const int vid = v0 + vl;
-        const bool act = vid < nv && dJdw[ri.vox_base + vid] != 0.f;
-        {
-            const float vx = (((vid % n)) + 0.5f) * inv, vy = (((vid / n) % n) + 0.5f) * inv, vz = ((vid / (n * n)) + 0.5f) * inv;
-            for (int q = part * 8; q < part * 8 + 8; ++q) {
-                const float t = 2.0f * fmaf(Bs[3 * q + 2], vz, fmaf(Bs[3 * q + 1], vy, Bs[3 * q] * vx));
-                float sn, cs;
-                sincospif(t, &sn, &cs);
-                gam[vl][q] = act ? cs : 0.f;
-                gam[vl][32 + q] = act ? sn : 0.f;
-            }
-        }
-        __syncthreads();
-        for (int o = part * 16; o < part * 16 + 16; ++o) {
-            float a = b1[o];
-#pragma unroll 8
-            for (int jj = 0; jj < 64; ++jj) a = fmaf(W1[o * 64 + jj], gam[vl][jj], a);
-            h1[vl][o] = act ? tanhf(a) : 0.f;
-        }
-        __syncthreads();
-        for (int o = part * 16; o < part * 16 + 16; ++o) {
-            float a = b2[o];
-#pragma unroll 8
-            for (int jj = 0; jj < 64; ++jj) a = fmaf(W2[o * 64 + jj], h1[vl][jj], a);
-            h2[vl][o] = act ? tanhf(a) : 0.f;
-        }
-        __syncthreads();
-        if (part == 0) {
-            float o5 = b3s;
-            for (int jj = 0; jj < 64; ++jj) o5 = fmaf(w3[jj], h2[vl][jj], o5);
-            const float w = 1.0f / (1.0f + expf(-o5));
-            gv5[vl] = act ? dJdw[ri.vox_base + vid] * w * (1.0f - w) : 0.f;
-        }
-        __syncthreads();
-        // W3 row 5 and b3[5] gradients (threads 0..63 own one entry each of W3 row 5)
-        if (tid < 64) {
-            float sacc = 0.f;
-            for (int vv = 0; vv < 64; ++vv) sacc = fmaf(gv5[vv], h2[vv][tid], sacc);
-            aW3 += sacc;
-        }
-        if (tid == 64) {
-            float sacc = 0.f;
-            for (int vv = 0; vv < 64; ++vv) sacc += gv5[vv];
-            aB3 += sacc;
-        }
-        __syncthreads();
-        // d2 = g5 w3 (1 - h2^2)
-        for (int o = part * 16; o < part * 16 + 16; ++o) {
-            const float hh = h2[vl][o];
-            d2[vl][o] = gv5[vl] * w3[o] * (1.0f - hh * hh);
-        }
-        __syncthreads();
-        // d1 = (W2^T d2) (1 - h1^2)
-        for (int o = part * 16; o < part * 16 + 16; ++o) {
-            float a = 0.f;
-#pragma unroll 8
-            for (int ii = 0; ii < 64; ++ii) a = fmaf(W2[ii * 64 + o], d2[vl][ii], a);
-            const float hh = h1[vl][o];
-            d1[vl][o] = a * (1.0f - hh * hh);
-        }
-        __syncthreads();
-        // outer products over the tile's voxels; entry e = tid + 256 m is row
-        // (tid >> 6) + 4 m, column tid & 63 of W1 / W2
-        {
-            const int ij = tid & 63, oi0 = tid >> 6;
-#pragma unroll 2
-            for (int vv = 0; vv < 64; ++vv) {
-                const float gj = gam[vv][ij], hj = h1[vv][ij];
+    for (int v0 = 0; v0 < nv; v0 += MBV) {
+        const int vid = v0 + 16 * wave + col, row = (16 * wave + col) * MROW;
+        const float dJ = vid < nv ? dJdw[ri.vox_base + vid] : 0.f;
+        const bool act = vid < nv && dJ != 0.f;
+        if (v0 + 16 * wave < nv) {
+            // W2 is read for every tile (from the caches): held in registers beside
+            // W1 and the sums it would spill
+            int wo = 64 * perm + kq, wt = 64 * kq + perm;
+            __asm__ volatile("" : "+v"(wo), "+v"(wt));
+            const float *w2 = g + OFF_W2 + wo, *w2t = g + OFF_W2 + wt;
+            float h1[16], h2[16];
+            {
+                const float vx = (((vid % n)) + 0.5f) * inv, vy = (((vid / n) % n) + 0.5f) * inv,
+                            vz = ((vid / (n * n)) + 0.5f) * inv;
+                float gam[16];
 #pragma unroll
-                for (int m = 0; m < 16; ++m) {
-                    aW1[m] = fmaf(d1[vv][oi0 + 4 * m], gj, aW1[m]);
-                    aW2[m] = fmaf(d2[vv][oi0 + 4 * m], hj, aW2[m]);
+                for (int b = 0; b < 8; ++b) {
+                    const int q = 4 * b + kq;
+                    const float t = 2.0f * fmaf(Bs[3 * q + 2], vz, fmaf(Bs[3 * q + 1], vy, Bs[3 * q] * vx));
+                    float sn, cs;
+                    sincospif(t, &sn, &cs);
+                    gam[b] = act ? cs : 0.f;
+                    gam[8 + b] = act ? sn : 0.f;
+                }
+                f32x4 acc[4];
+#pragma unroll
+                for (int m = 0; m < 4; ++m)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) acc[m][i] = b1s[16 * m + 4 * i + kq];
+#pragma unroll
+                for (int b = 0; b < 16; ++b) {
+                    gamS[row + 4 * b + kq] = gam[b];
+#pragma unroll
+                    for (int m = 0; m < 4; ++m)
+                        acc[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(w1[m][b], gam[b], acc[m], 0, 0, 0);
+                }
+#pragma unroll
+                for (int b = 0; b < 16; ++b) {
+                    h1[b] = act ? tanhf(acc[b >> 2][b & 3]) : 0.f;
+                    h1S[row + 4 * b + kq] = h1[b];
                 }
             }
-        }
-        if (tid < 64) {
-            float s1 = 0.f, s2 = 0.f;
-            for (int vv = 0; vv < 64; ++vv) {
-                s1 += d1[vv][tid];
-                s2 += d2[vv][tid];
+            {
+                f32x4 acc[4];
+#pragma unroll
+                for (int m = 0; m < 4; ++m)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) acc[m][i] = b2s[16 * m + 4 * i + kq];
+#pragma unroll
+                for (int b = 0; b < 16; ++b)
+#pragma unroll
+                    for (int m = 0; m < 4; ++m)
+                        acc[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(w2[64 * 16 * m + 4 * b], h1[b], acc[m], 0, 0, 0);
+#pragma unroll
+                for (int b = 0; b < 16; ++b) h2[b] = act ? tanhf(acc[b >> 2][b & 3]) : 0.f;
             }
-            aB1 += s1;
-            aB2 += s2;
+            f32x4 head;  // row 0: the sigmoid logit
+#pragma unroll
+            for (int i = 0; i < 4; ++i) head[i] = lane < 16 && i == 0 ? b3 : 0.f;
+#pragma unroll
+            for (int b = 0; b < 16; ++b)
+                head = __builtin_amdgcn_mfma_f32_16x16x4f32(col == 0 ? w3s[4 * b + kq] : 0.f, h2[b], head, 0, 0, 0);
+            const float o5 = __shfl(head[0], col, 64);
+            const float w = 1.0f / (1.0f + expf(-o5));
+            const float g5 = act ? dJ * w * (1.0f - w) : 0.f;
+            s5 += sum16(g5);
+            f32x4 acc[4];
+#pragma unroll
+            for (int m = 0; m < 4; ++m)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) acc[m][i] = 0.f;
+            // d2 = g5 w3 (1 - h2^2), d1 = (W2^T d2) (1 - h1^2)
+#pragma unroll
+            for (int b = 0; b < 16; ++b) {
+                const float hh = h2[b];
+                const float d2 = g5 * w3s[4 * b + kq] * (1.0f - hh * hh);
+                d2S[row + 4 * b + kq] = d2;
+#pragma unroll
+                for (int m = 0; m < 4; ++m)
+                    acc[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(w2t[64 * 4 * b + 16 * m], d2, acc[m], 0, 0, 0);
+                s2[b] += sum16(d2);
+                s3[b] += sum16(g5 * hh);
+            }
+#pragma unroll
+            for (int b = 0; b < 16; ++b) {
+                const float hh = h1[b];
+                const float d1 = acc[b >> 2][b & 3] * (1.0f - hh * hh);
+                d1S[row + 4 * b + kq] = d1;
+                s1[b] += sum16(d1);
+            }
         }
+        __syncthreads();
+        // outer products over the tile's waves that hold voxels; k = voxel
+        const int left = (nv - v0 + 15) / 16 * 16, ke = left < MBV ? left : MBV;
+        for (int q = 0; q < ke; q += 16)
+#pragma unroll
+            for (int v = 0; v < 16; v += 4) {
+                const int at = (q + v + kq) * MROW + col;
+                const float f1 = d1S[at + 16 * rb], f2 = d2S[at + 16 * rb];
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    a1[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(f1, gamS[at + 16 * (cb + e)], a1[e], 0, 0, 0);
+                    a2[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(f2, h1S[at + 16 * (cb + e)], a2[e], 0, 0, 0);
+                }
+            }
         __syncthreads();
     }
 #pragma unroll
-    for (int m = 0; m < 16; ++m) {
-        const int e = tid + 256 * m;
-        out[OFF_W1 + e] = aW1[m];
-        out[OFF_W2 + e] = aW2[m];
+    for (int e = 0; e < 2; ++e)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int at = 64 * (16 * rb + 4 * kq + i) + 16 * (cb + e) + col;
+            out[OFF_W1 + at] = a1[e][i];
+            out[OFF_W2 + at] = a2[e][i];
+        }
+    // the waves' sums, in wave order (the tiles' LDS is free now)
+    if (col == 0) {
+#pragma unroll
+        for (int b = 0; b < 16; ++b) {
+            gamS[64 * wave + 4 * b + kq] = s1[b];
+            h1S[64 * wave + 4 * b + kq] = s2[b];
+            d1S[64 * wave + 4 * b + kq] = s3[b];
+        }
+        if (kq == 0) d2S[wave] = s5;
     }
+    __syncthreads();
     if (tid < 64) {
-        out[OFF_B1 + tid] = aB1;
-        out[OFF_B2 + tid] = aB2;
-        for (int row = 0; row < 6; ++row) out[OFF_W3 + row * 64 + tid] = row == 5 ? aW3 : 0.f;
+        float t1 = 0.f, t2 = 0.f, t3 = 0.f;
+        for (int q = 0; q < MBT / 64; ++q) {
+            t1 += gamS[64 * q + tid];
+            t2 += h1S[64 * q + tid];
+            t3 += d1S[64 * q + tid];
+        }
+        out[OFF_B1 + tid] = t1;
+        out[OFF_B2 + tid] = t2;
+        for (int q = 0; q < 6; ++q) out[OFF_W3 + q * 64 + tid] = q == 5 ? t3 : 0.f;
     }
     if (tid < 5) out[OFF_B3 + tid] = 0.f;  // class logits carry no gradient
-    if (tid == 64) out[OFF_B3 + 5] = aB3;
+    if (tid == 64) {
+        float t5 = 0.f;
+        for (int q = 0; q < MBT / 64; ++q) t5 += d2S[q];
+        out[OFF_B3 + 5] = t5;
+    }
 }
 
 typedef void (*AdjFn)(AArgs);
@@ -1134,7 +1205,7 @@ hipError_t launch_adj_genome(const RobotInfo *robots, int R, int total_vox, cons
     hipLaunchKernelGGL(k_adj_dw, dim3((total_vox + 255) / 256), dim3(256), 0, st, A);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_mlp_backward, dim3(R), dim3(256), 0, st, robots, genomes, B, dJdw, g_gen);
+    hipLaunchKernelGGL(k_mlp_backward, dim3(R), dim3(MBT), 0, st, robots, genomes, B, dJdw, g_gen);
     return hipGetLastError();
 }
 

@@ -233,6 +233,41 @@ def test_genome_gradient_matches_oracle(orc):
         assert e <= TOL
 
 
+@pytest.mark.parametrize("side", [2, 5, 6, 8, 9])
+def test_genome_gradient_at_tile_edges(orc, side):
+    """The genome gradient from the GPU's own spring gradients, carried on in
+    FP64 (parallel-sum rule and MLP), so that only that part is compared.  Tiles
+    of 128 voxels (16 per wave): 8 voxels, 125 (a partial last wave), 216 and 729
+    (a partial last tile), 512 (whole tiles)."""
+    from paper_2405_00698_amd.api import Population
+    R, steps, K = 4, 60, 30
+    B = inputs.gaussian_B()
+    G = inputs.random_genomes(R, seed=60 + side, empty_bias=np.full(R, -3.0 if side == 2 else 0.0))
+    P = Population([side] * R)
+    Gt, Bt = torch.from_numpy(G).to(DEV), torch.from_numpy(B).to(DEV)
+    P.build_from_genomes(Gt, Bt, SR_QUERY_FP32)
+    P.record(K, steps)
+    P.step(steps)
+    g = P.backward(torch.from_numpy(_dJ(R, 2)).to(DEV), genomes=Gt, B=Bt)
+    gg = g["genome"].cpu().numpy().astype(np.float64)
+    gk, ga = (g[q].cpu().numpy().astype(np.float64) for q in ("k", "a"))
+    cls, w = (q.cpu().numpy() for q in P.query())
+    _, S, _, so = P.counts()
+    for r in range(R):
+        vox = slice(r * side ** 3, (r + 1) * side ** 3)
+        robot = orc.Robot(side, cls[vox], w[vox].astype(np.float64))
+        sp = robot.springs()
+        sl = slice(so[r], so[r + 1])
+        assert robot.S == S[r]
+        # dJ/dk at fixed Z = k a (phases are zero here, and dJ/dIm Z carries no weight)
+        gz = ga[sl] / sp["k"]
+        dJdw = robot.dJdw(gk[sl] - sp["a"] * gz, gz, np.zeros_like(gz))
+        go = orc.mlp_backward(G[r].astype(np.float64), B.astype(np.float64), side, dJdw)
+        e = _l2rel(gg[r], go)
+        say("side", side, "robot", r, "genome gradient relative L2 %.2e" % e)
+        assert e <= TOL
+
+
 def test_autograd_functions_route_through_the_adjoint():
     from paper_2405_00698_amd.api import GenomeFitness, Population, SpringFitness
     cls, w = voxel_population(C1, 53)
