@@ -105,8 +105,11 @@ hipError_t launch_build_mesh(const RobotInfo *robots, int R, int max_side, bool 
 hipError_t launch_finish_build(const RobotInfo *robots, int R, uint8_t *bad_class, int64_t *mass_off,
                                int64_t *spring_off, int64_t *step, int64_t *host, hipStream_t st);
 
-hipError_t launch_query(const RobotInfo *robots, int R, int max_side, const float *genomes, const float *B,
-                        int precision, uint8_t *cls, float *w, hipStream_t st);
+// bytes of the encoding table launch_query takes for this population (0: none)
+size_t query_table_bytes(const RobotInfo *robots, int R);
+// sides: bit n set when a robot of side n is present
+hipError_t launch_query(const RobotInfo *robots, int R, uint32_t sides, const float *genomes, const float *B,
+                        int precision, void *table, uint8_t *cls, float *w, hipStream_t st);
 
 hipError_t launch_ga(const float *fit, const float *gin, float *gout, int P, int L, int E, int k, uint64_t pc,
                      uint64_t pm, float sigma, uint64_t seed, uint64_t gen, int32_t *dec, hipStream_t st);

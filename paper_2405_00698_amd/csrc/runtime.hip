@@ -113,6 +113,8 @@ struct sr_pop {
     int sticky = 0;
     // genome query scratch
     uint8_t *q_cls = nullptr;
+    char *q_table = nullptr;  // the encoding of every side's voxels (large populations)
+    uint32_t sides = 0;       // bit n: some robot has side n
     int32_t *vox_robot = nullptr;
     // adjoint: checkpoints of (x, v) at steps 0, K, 2K, ... since the build
     int ck_every = 0, ck_cap = 0, ck_alloc = 0;
@@ -186,7 +188,7 @@ void pop_free(sr_pop *pop) {
                     pop->ix.base, pop->ix.mask, pop->x0, pop->xbuf[0], pop->xbuf[1], pop->vbuf[0], pop->vbuf[1],
                     pop->slot_node, pop->slot_robot,
                     pop->bad_class, pop->diverged, pop->d_step, pop->sc, pop->d_lists, pop->d_mass_off,
-                    pop->d_spring_off, pop->q_cls, pop->vox_robot, pop->ck_x, pop->ck_v,
+                    pop->d_spring_off, pop->q_cls, pop->q_table, pop->vox_robot, pop->ck_x, pop->ck_v,
                     pop->lx, pop->lv, pop->gk, pop->gs, pop->gc, pop->gd, pop->dJdw, pop->adj_sc};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
@@ -378,6 +380,7 @@ int pop_create(const sr_sim_params *params, int32_t n_robots, const int32_t *gri
         slots += ri.slots;
         vox += (int64_t)ri.n * ri.n * ri.n;
         by_side[ri.n].push_back(r);
+        pop->sides |= 1u << ri.n;
         if (ri.n > pop->max_side) pop->max_side = ri.n;
     }
     if (slots * 2 * NDIR >= INT32_MAX) {
@@ -420,6 +423,8 @@ int pop_create(const sr_sim_params *params, int32_t n_robots, const int32_t *gri
     ALLOC(pop->d_mass_off, (size_t)n_robots + 1);
     ALLOC(pop->d_spring_off, (size_t)n_robots + 1);
     ALLOC(pop->q_cls, (size_t)vox);
+    if (query_table_bytes(pop->h_robots.data(), n_robots) > 0)
+        ALLOC(pop->q_table, query_table_bytes(pop->h_robots.data(), n_robots));
     ALLOC(pop->vox_robot, (size_t)vox);
 #undef ALLOC
     if (e == hipSuccess)
@@ -542,7 +547,8 @@ int pop_build_from_genomes(sr_pop *pop, const float *genomes, const float *B, in
     if (!genomes || !B) return set_err(SR_EINVAL, "null genome or B");
     if (precision != SR_QUERY_FP32 && precision != SR_QUERY_BF16)
         return set_err(SR_EINVAL, "unknown query precision %d", precision);
-    HIPC(pop, launch_query(pop->d_robots, pop->R, pop->max_side, genomes, B, precision, pop->q_cls, pop->w, pop->st));
+    HIPC(pop, launch_query(pop->d_robots, pop->R, pop->sides, genomes, B, precision, pop->q_table, pop->q_cls, pop->w,
+                           pop->st));
     return pop_build_from_voxels(pop, pop->q_cls, pop->w);
 }
 
@@ -1107,12 +1113,15 @@ int pop_backward(sr_pop *pop, const float *dJ_dfitness, float *g_k, float *g_a, 
         for (int g : pop->rec_order) {
             if (!split(g)) continue;
             const SideGroup &gr = pop->groups[g];
-            HIPC(pop, hipStreamWaitEvent(sum_st, event(REVERSED, g, b), 0));
+            // the first segment's passes, the last to run, each on its group's own lane
+            hipStream_t st = seg == 0 ? lane(g) : sum_st;
+            if (seg == 0 && nseg > 1) HIPC(pop, hipStreamWaitEvent(st, event(SUMMED, g, 1), 0));
+            HIPC(pop, hipStreamWaitEvent(st, event(REVERSED, g, b), 0));
             HIPC(pop, launch_adj_grad(gr.n, pop->phase, pop->d_robots, pop->d_lists + gr.offset, gr.count, pop->pl,
                                       pop->x0, pop->rec_x[b], pop->rec_u[b], pop->rec_l[b], steps(seg),
                                       pop->adj_sc + (int64_t)seg * K, pop->gk, pop->gs, pop->gc, pop->gd, pop->c,
-                                      sum_st));
-            HIPC(pop, hipEventRecord(event(SUMMED, g, b), sum_st));
+                                      st));
+            HIPC(pop, hipEventRecord(event(SUMMED, g, b), st));
         }
         return SR_OK;
     };
