@@ -4,6 +4,7 @@ Argument marshalling only: every step of the hot path runs in the HIP
 library.  Torch tensors supply device memory and the stream."""
 import ctypes as C
 
+import numpy as np
 import torch
 
 from . import _lib
@@ -147,12 +148,10 @@ class Population:
     # ---------------------------------------------------------------- introspection
     def counts(self):
         if self._counts is None:
-            M = (C.c_int32 * self.R)()
-            S = (C.c_int32 * self.R)()
-            mo = (C.c_int64 * (self.R + 1))()
-            so = (C.c_int64 * (self.R + 1))()
-            check(_lib.load().pop_get_counts(self.h, M, S, mo, so))
-            self._counts = (list(M), list(S), list(mo), list(so))
+            # numpy buffers: tolist makes the Python ints in one C loop
+            out = [np.empty(self.R + i // 2, np.int64 if i >= 2 else np.int32) for i in range(4)]
+            check(_lib.load().pop_get_counts(self.h, *[q.ctypes.data for q in out]))
+            self._counts = tuple(q.tolist() for q in out)
         return self._counts
 
     def voxels(self):
