@@ -84,9 +84,23 @@ __device__ __forceinline__ void spring_grad_sums(float r2, float ir, float kL, f
 // writes each step's lambda_F to rec_l instead, and k_adj_grad forms the sums
 // from the recorded positions and those lambda_F afterwards.  The 13 springs'
 // three sums per slot no longer take registers beside the adjoint recursion.
+// GPAR (split chunked form): each chunk's spring parameters are read from the
+// planes for every step (they stay in L2), issued after the previous chunk's
+// forward half and so in flight over its barrier and receiving half, instead
+// of held for all 13 directions of every slot: at 10^3-12^3 those did not fit
+// the registers beside the recursion and were spilled to scratch, which reads
+// the same bytes without overlap.  With dashpots (four planes) it is the better
+// form from 10^3 on, without (two or three planes) only at 12^3: at 10^3 and
+// 11^3 the held parameters spill 0 to 33 registers, and the extra reads cost
+// more (11^3, 256 robots: 9.6 ms a backward of 400 steps held, 10.3 read).
+// Together with the gradient pass in four parts: backward of 400 steps, Table II
+// model, 64 robots of 10^3 / 11^3 / 12^3 7.6 / 13.6 / 27.6 -> 6.1 / 7.8 / 12.8 ms,
+// 256 robots 17.0 / 33.6 / 63.2 -> 13.2 / 21.2 / 27.7 ms (12^3 with the recording
+// kernel of its own); without dashpots 256 of 12^3 16.4 -> 15.4 ms.
 template <int N, int BS, bool PHASE, bool XCH, int ALAG = 0, bool ONEBUF = false, bool DASH = false, bool FNC = false,
-          bool NOG = false, int XCC = 1>
+          bool NOG = false, int XCC = 1, bool GPAR = false>
 __global__ __launch_bounds__(BS) void k_adjoint(AArgs A) {
+    static_assert(!GPAR || (XCH && NOG && XCC > 1), "parameters per chunk are a form of the split chunked exchange");
     static_assert(XCC == 1 || XCH, "direction chunks are a form of the exchange");
     static_assert(ALAG == 0 || XCH, "pipelined reads are for the exchange form");
     static_assert(!DASH || XCH || ONEBUF, "the dashpot adjoint keeps one buffer");
@@ -132,11 +146,13 @@ __global__ __launch_bounds__(BS) void k_adjoint(AArgs A) {
 
         bool pres[NPT];
         float3 X0[NPT], lx[NPT], lv[NPT];
-        float pk[NPT][NDIR], pa[NPT][NDIR], pb[NPT][NDIR], pik[NPT][NDIR];
+        constexpr int NP = GPAR ? NDC : NDIR;  // directions whose parameters are held
+        auto pi_ = [&](int d) { return GPAR ? d % NDC : d; };
+        float pk[NPT][NP], pa[NPT][NP], pb[NPT][NP], pik[NPT][NOG ? 1 : NDIR];
         float qk[NPT][NQ], qa[NPT][NQ], qb[NPT][NQ];
         constexpr int NG = NOG ? 1 : NDIR;
         float gk[NPT][NG], gs[NPT][NG], gc[NPT][NG];
-        float pd[NPT][DASH ? NDIR : 1], qd[NPT][DASH ? NQ : 1], gd[NPT][DASH && !NOG ? NDIR : 1];
+        float pd[NPT][DASH ? NP : 1], qd[NPT][DASH ? NQ : 1], gd[NPT][DASH && !NOG ? NDIR : 1];
 #pragma unroll
         for (int k = 0; k < NPT; ++k) {
             const int s = tid + k * BS;
@@ -150,13 +166,14 @@ __global__ __launch_bounds__(BS) void k_adjoint(AArgs A) {
             lv[k] = make_float3(LV.x, LV.y, LV.z);
 #pragma unroll
             for (int d = 0; d < NDIR; ++d) {
+                if (d >= NP) continue;  // GPAR: the first chunk's
                 const int pi = pbase + d * SL + sc_;
                 const float kk = live ? A.pl.k[pi] : 0.f;
                 pk[k][d] = kk;
                 pa[k][d] = live ? A.pl.kal[pi] : 0.f;
                 pb[k][d] = (live && PHASE) ? A.pl.kbe[pi] : 0.f;
-                pik[k][d] = kk != 0.f ? 1.0f / kk : 0.f;
                 if constexpr (!NOG) {
+                    pik[k][d] = kk != 0.f ? 1.0f / kk : 0.f;
                     gk[k][d] = live ? A.gk[pi] : 0.f;
                     gs[k][d] = live ? A.gs[pi] : 0.f;
                     gc[k][d] = live ? A.gc[pi] : 0.f;
@@ -361,9 +378,10 @@ __global__ __launch_bounds__(BS) void k_adjoint(AArgs A) {
                     const float ux = LJ.x - LF[k].x, uy = LJ.y - LF[k].y, uz = LJ.z - LF[k].z;
                     const float r2 = len2(dx, dy, dz);
                     const float ir = __builtin_amdgcn_rsqf(r2);
-                    float kL = fmaf(pa[k][d], sct.x, pk[k][d] * L0d(c, d));
-                    if (PHASE) kL = fmaf(pb[k][d], sct.y, kL);
-                    const float c1 = fmaf(-kL, ir, pk[k][d]);
+                    const float kk = pk[k][pi_(d)];
+                    float kL = fmaf(pa[k][pi_(d)], sct.x, kk * L0d(c, d));
+                    if (PHASE) kL = fmaf(pb[k][pi_(d)], sct.y, kL);
+                    const float c1 = fmaf(-kL, ir, kk);
                     const float du = fmaf(dz, uz, fmaf(dy, uy, dx * ux));
                     const float c2 = (kL * ir) * ir * ir * du;
                     float kx = fmaf(c1, ux, c2 * dx), ky = fmaf(c1, uy, c2 * dy), kz = fmaf(c1, uz, c2 * dz);
@@ -372,7 +390,7 @@ __global__ __launch_bounds__(BS) void k_adjoint(AArgs A) {
                         const float3 VJ = ld3(vsb + (PAD + dir_off(d, N)));
                         const float3 VI = Vr[DASH ? k : 0];
                         const float wx = VJ.x - VI.x, wy = VJ.y - VI.y, wz = VJ.z - VI.z;
-                        const float cd = pd[k][DASH ? d : 0];
+                        const float cd = pd[k][DASH ? pi_(d) : 0];
                         const float ir2 = ir * ir;
                         const float wv = fmaf(dz, wz, fmaf(dy, wy, dx * wx));
                         const float ce = cd * ir2, q2 = -2.f * wv * du * ir2;
@@ -397,7 +415,7 @@ __global__ __launch_bounds__(BS) void k_adjoint(AArgs A) {
                         ku[(2 * NDC + d - d0) * CL + PAD + s] = kz;
                     }
                     if constexpr (!NOG)
-                        spring_grad_sums(r2, ir, kL, du, pk[k][d], pik[k][d], sct, gk[k][NOG ? 0 : d], gs[k][NOG ? 0 : d],
+                        spring_grad_sums(r2, ir, kL, du, kk, pik[k][NOG ? 0 : d], sct, gk[k][NOG ? 0 : d], gs[k][NOG ? 0 : d],
                                          gc[k][NOG ? 0 : d]);
                     if (FNC) __builtin_amdgcn_sched_barrier(0);
                 }
@@ -442,6 +460,25 @@ __global__ __launch_bounds__(BS) void k_adjoint(AArgs A) {
                 }
                 accs[k] = acc;
                 if constexpr (DASH) accv[DASH ? k : 0] = av;
+            }
+            if constexpr (GPAR) {
+                // the next chunk's parameters (after the last, the next step's first)
+                const int n0 = ch + 1 < NCH ? d1 : 0;
+#pragma unroll
+                for (int k = 0; k < NPT; ++k) {
+                    int s = tid + k * BS;
+                    __asm__ volatile("" : "+v"(s));  // not out of the time loop
+#pragma unroll
+                    for (int j = 0; j < NDC; ++j) {
+                        const int d = n0 + j;
+                        if (d >= NDIR || !pres[k]) continue;
+                        const int pi = pbase + d * SL + s;
+                        pk[k][j] = A.pl.k[pi];
+                        pa[k][j] = A.pl.kal[pi];
+                        if (PHASE) pb[k][j] = A.pl.kbe[pi];
+                        if constexpr (DASH) pd[k][DASH ? j : 0] = A.pl.kd[pi];
+                    }
+                }
             }
             if (XCH) {
                 __syncthreads();
@@ -664,23 +701,35 @@ __device__ __forceinline__ void adj_grad_robot(const AArgs &A, int q, float4 *xs
     }
 }
 
-// The gradient pass over directions D0 .. D1 - 1, or (D2 > D1) over D0 .. D1 - 1
-// in the workgroups with blockIdx.y 0 and D1 .. D2 - 1 in those with 1: the two
-// halves of a robot run side by side (they write disjoint sums).
+// The gradient pass over all directions in one workgroup per robot (PARTS 1),
+// or over 0..6 and 7..12 in two (PARTS 2), or over 0..3, 4..6, 7..9 and 10..12
+// in four side by side (blockIdx.y; they write disjoint sums).  The parts are
+// what a thread's slots hold in registers: with two parts the 2 or 3 slots of a
+// thread at 10^3-12^3 spilled 100 to 430 registers (12^3 with dashpots: 11.5 us
+// a step, in four parts GRAD4 us).
 // DASH: also dJ/dc of the spring dashpots, from the recorded velocities v_n.
-template <int N, int BS, bool PHASE, int D0, int D1, int D2 = D1, bool DASH = false>
+template <int N, int BS, bool PHASE, int PARTS, bool DASH = false>
 __global__ __launch_bounds__(BS) void k_adj_grad(AArgs A) {
     __shared__ float4 xs[Geo<N>::XL];
     __shared__ float4 lf[Geo<N>::XL];
     __shared__ float4 vs[DASH ? Geo<N>::XL : 1];
     for (int q = blockIdx.x; q < A.count; q += gridDim.x) {
-        if constexpr (D2 == D1) {
-            adj_grad_robot<N, BS, PHASE, D0, D1, DASH>(A, q, xs, lf, vs);
+        if constexpr (PARTS == 1) {
+            adj_grad_robot<N, BS, PHASE, 0, 13, DASH>(A, q, xs, lf, vs);
+        } else if constexpr (PARTS == 2) {
+            if (blockIdx.y == 0)
+                adj_grad_robot<N, BS, PHASE, 0, 7, DASH>(A, q, xs, lf, vs);
+            else
+                adj_grad_robot<N, BS, PHASE, 7, 13, DASH>(A, q, xs, lf, vs);
         } else {
             if (blockIdx.y == 0)
-                adj_grad_robot<N, BS, PHASE, D0, D1, DASH>(A, q, xs, lf, vs);
+                adj_grad_robot<N, BS, PHASE, 0, 4, DASH>(A, q, xs, lf, vs);
+            else if (blockIdx.y == 1)
+                adj_grad_robot<N, BS, PHASE, 4, 7, DASH>(A, q, xs, lf, vs);
+            else if (blockIdx.y == 2)
+                adj_grad_robot<N, BS, PHASE, 7, 10, DASH>(A, q, xs, lf, vs);
             else
-                adj_grad_robot<N, BS, PHASE, D1, D2, DASH>(A, q, xs, lf, vs);
+                adj_grad_robot<N, BS, PHASE, 10, 13, DASH>(A, q, xs, lf, vs);
         }
     }
 }
@@ -1031,7 +1080,7 @@ struct AdjEntry {
     AdjFn fn, fn_phase;
     // split form: fn is the reverse step without gradient sums, and the
     // gradient pass g0 runs gblock threads per workgroup on a grid of robots
-    // x gy (gy 2: directions 0..6 and 7..12 in workgroups side by side)
+    // x gy (parts of the directions in workgroups side by side)
     int gblock = 0;
     AdjFn g0 = nullptr, g0_phase = nullptr;
     int gy = 1;
@@ -1045,27 +1094,21 @@ struct AdjEntry {
     {                                                                                                          \
         NN, BS, k_adjoint<NN + 1, BS, false, true, LG, false, false, false, true>,                              \
             k_adjoint<NN + 1, BS, true, true, LG, false, false, false, true>, GBS,                              \
-            k_adj_grad<NN + 1, GBS, false, 0, 13>, k_adj_grad<NN + 1, GBS, true, 0, 13>                          \
+            k_adj_grad<NN + 1, GBS, false, 1>, k_adj_grad<NN + 1, GBS, true, 1>                                  \
     }
 // split exchange form in XC direction chunks (one chunk's rows in LDS at a
-// time), the gradient pass over all directions in one workgroup per robot
-// (SR_AESC1) or in two side by side (SR_AESC)
-#define SR_AESC1(NN, BS, LG, XC, GBS)                                                                           \
+// time), parameters per chunk with GP, the gradient pass in GY workgroups per
+// robot
+#define SR_AESC(NN, BS, LG, XC, GP, GBS, GY)                                                                    \
     {                                                                                                          \
-        NN, BS, k_adjoint<NN + 1, BS, false, true, LG, false, false, false, true, XC>,                          \
-            k_adjoint<NN + 1, BS, true, true, LG, false, false, false, true, XC>, GBS,                          \
-            k_adj_grad<NN + 1, GBS, false, 0, 13>, k_adj_grad<NN + 1, GBS, true, 0, 13>                          \
-    }
-#define SR_AESC(NN, BS, LG, XC, GBS)                                                                            \
-    {                                                                                                          \
-        NN, BS, k_adjoint<NN + 1, BS, false, true, LG, false, false, false, true, XC>,                          \
-            k_adjoint<NN + 1, BS, true, true, LG, false, false, false, true, XC>, GBS,                          \
-            k_adj_grad<NN + 1, GBS, false, 0, 7, 13>, k_adj_grad<NN + 1, GBS, true, 0, 7, 13>, 2                 \
+        NN, BS, k_adjoint<NN + 1, BS, false, true, LG, false, false, false, true, XC, GP>,                      \
+            k_adjoint<NN + 1, BS, true, true, LG, false, false, false, true, XC, GP>, GBS,                      \
+            k_adj_grad<NN + 1, GBS, false, GY>, k_adj_grad<NN + 1, GBS, true, GY>, GY                            \
     }
 const AdjEntry kAdj[] = {SR_AE(1, 64, true),    SR_AE(2, 64, true),    SR_AE(3, 64, true),   SR_AEL(4, 128, 2),
                          SR_AEL(5, 256, 2),     SR_AEL(6, 384, 2),     SR_AEL(7, 512, 2),    SR_AESL(8, 768, 2, 768),
-                         SR_AESC1(9, 1024, 2, 2, 1024), SR_AESC(10, 768, 2, 3, 704), SR_AESC(11, 1024, 0, 4, 1024),
-                         SR_AESC(12, 768, 0, 7, 768)};
+                         SR_AESC(9, 1024, 2, 2, false, 1024, 1), SR_AESC(10, 768, 2, 3, false, 704, 2),
+                         SR_AESC(11, 1024, 0, 4, false, 1024, 2), SR_AESC(12, 768, 0, 7, true, 768, 4)};
 // spring dashpots or the damped ground (Table II model): the one-buffer
 // recompute form with the velocity terms
 #define SR_AED(NN, BS) \
@@ -1078,17 +1121,18 @@ const AdjEntry kAdj[] = {SR_AE(1, 64, true),    SR_AE(2, 64, true),    SR_AE(3, 
             k_adjoint<NN + 1, BS, true, true, 0, false, true, false, false, XC>                                 \
     }
 // split form of the above: the reverse recursion alone, then the gradient
-// pass with the dashpot terms in two direction halves side by side
-#define SR_AEDS(NN, BS, XC, GBS)                                                                               \
+// pass with the dashpot terms in GY workgroups per robot
+#define SR_AEDS(NN, BS, XC, GP, GBS, GY)                                                                       \
     {                                                                                                          \
-        NN, BS, k_adjoint<NN + 1, BS, false, true, 0, false, true, false, true, XC>,                            \
-            k_adjoint<NN + 1, BS, true, true, 0, false, true, false, true, XC>, GBS,                            \
-            k_adj_grad<NN + 1, GBS, false, 0, 7, 13, true>, k_adj_grad<NN + 1, GBS, true, 0, 7, 13, true>, 2     \
+        NN, BS, k_adjoint<NN + 1, BS, false, true, 0, false, true, false, true, XC, GP>,                        \
+            k_adjoint<NN + 1, BS, true, true, 0, false, true, false, true, XC, GP>, GBS,                        \
+            k_adj_grad<NN + 1, GBS, false, GY, true>, k_adj_grad<NN + 1, GBS, true, GY, true>, GY                \
     }
 const AdjEntry kAdjD[] = {SR_AED(1, 64),        SR_AED(2, 64),        SR_AED(3, 64),        SR_AEDX(4, 128, 1),
-                          SR_AEDX(5, 256, 1),   SR_AEDX(6, 384, 1),   SR_AEDX(7, 512, 1),   SR_AEDS(8, 768, 2, 768),
-                          SR_AEDS(9, 1024, 3, 1024), SR_AEDS(10, 768, 5, 768), SR_AEDS(11, 1024, 7, 1024),
-                          SR_AEDS(12, 768, 13, 768)};
+                          SR_AEDX(5, 256, 1),   SR_AEDX(6, 384, 1),   SR_AEDX(7, 512, 1),
+                          SR_AEDS(8, 768, 2, false, 768, 2), SR_AEDS(9, 1024, 3, false, 1024, 2),
+                          SR_AEDS(10, 768, 5, true, 768, 2), SR_AEDS(11, 1024, 7, true, 1024, 4),
+                          SR_AEDS(12, 768, 13, true, 768, 4)};
 
 }  // namespace
 
