@@ -462,22 +462,23 @@ int pop_create(const sr_sim_params *params, int32_t n_robots, const int32_t *gri
         }
     }
     // Recorded runs and reverse sweeps: the groups dealt, longest first, to the
-    // least loaded of REC_LANES streams, a group's time taken as its lattice
-    // points times its turns on 256 CUs.  Four lanes are what the device's four
-    // hardware queues run at once; a stream beyond them only waits behind
-    // another one.  From three groups on the last lane also carries the gradient
-    // passes of the reverse sweep (about a quarter of its time).
+    // least loaded of REC_LANES streams.  A group's time is its turns on 256 CUs
+    // times that of one robot on a CU, in us a step for recording and reversing
+    // (Table II model; sides up to 7^3 are latency bound and alike).  Four lanes
+    // are what the device's four hardware queues run at once; a stream beyond
+    // them only waits behind another one.  From three groups on the last lane
+    // also carries the gradient passes, counted in from the start.
     {
         const int G = (int)pop->groups.size();
-        auto cost = [&](int g) {
-            const double N = pop->groups[g].n + 1;
-            return N * N * N * ((pop->groups[g].count + 255) / 256);
-        };
+        static const double chain[SR_MAX_SIDE + 1] = {0, 5.5, 5.5, 5.5, 5.5, 5.5, 5.7, 5.9, 7.9, 10, 16, 20, 31};
+        static const double sums[SR_MAX_SIDE + 1] = {0, 0, 0, 0, 0, 0, 0, 0, 2, 2, 2.4, 4.5, 5.4};
+        auto turns = [&](int g) { return (pop->groups[g].count + 255) / 256; };
+        auto cost = [&](int g) { return chain[pop->groups[g].n] * turns(g); };
         double load[REC_LANES] = {};
         for (int g = 0; g < G; ++g) {
             pop->rec_order.push_back(g);
             if (G >= 3 && adjoint_is_split(pop->groups[g].n, pop->c.dash || pop->c.gdamp))
-                load[REC_LANES - 1] += 0.25 * cost(g);
+                load[REC_LANES - 1] += sums[pop->groups[g].n] * turns(g);
         }
         std::stable_sort(pop->rec_order.begin(), pop->rec_order.end(), [&](int a, int b) { return cost(a) > cost(b); });
         pop->rec_lane.assign(G, 0);
