@@ -757,7 +757,7 @@ __global__ void k_adj_init(const RobotInfo *robots, int total_slots, const int32
 }
 
 // Per spring: dJ/dk, dJ/da, dJ/dphi in canonical order, from the stencil sums.
-__global__ __launch_bounds__(EACH_SLOTS) void k_adj_springs(const RobotInfo *robots, int total_slots,
+__global__ __launch_bounds__(EACH_THREADS) void k_adj_springs(const RobotInfo *robots, int total_slots,
                                                             const int32_t *slot_robot, SpringIndex ix,
                                                             const int64_t *spring_off, Planes pl, float voxel_len,
                                                             const float *gk, const float *gs, const float *gc,
@@ -1217,7 +1217,7 @@ hipError_t launch_adj_springs(const RobotInfo *robots, int total_slots, const in
                               const int64_t *spring_off, Planes pl, float voxel_len, const float *gk, const float *gs,
                               const float *gc, float *g_k, float *g_a, float *g_phi, hipStream_t st) {
     if (!g_k && !g_a && !g_phi) return hipSuccess;
-    hipLaunchKernelGGL(k_adj_springs, dim3((total_slots + EACH_SLOTS - 1) / EACH_SLOTS), dim3(EACH_SLOTS), 0, st,
+    hipLaunchKernelGGL(k_adj_springs, dim3((total_slots + EACH_SLOTS - 1) / EACH_SLOTS), dim3(EACH_THREADS), 0, st,
                        robots, total_slots, slot_robot, ix, spring_off, pl, voxel_len, gk, gs, gc, g_k, g_a, g_phi);
     return hipGetLastError();
 }

@@ -1325,7 +1325,7 @@ __device__ __forceinline__ void spring_polar(float kL0, float kal, float kbe, fl
 }
 
 // The springs in canonical order: 24 B each, at the rate of memory.
-__global__ __launch_bounds__(EACH_SLOTS) void k_springs_io(const RobotInfo *robots, int total_slots,
+__global__ __launch_bounds__(EACH_THREADS) void k_springs_io(const RobotInfo *robots, int total_slots,
                                                            const int32_t *slot_robot, const int32_t *slot_node,
                                                            SpringIndex ix, const int64_t *spring_off, Planes pl,
                                                            float voxel_len, int32_t *ij, float *L0o, float *ko,
@@ -1734,7 +1734,7 @@ hipError_t launch_springs_io(const RobotInfo *robots, int R, int total_slots, co
                              float voxel_len, int32_t *ij, float *L0, float *k, float *a, float *phi,
                              const float *k_in, const float *a_in, const float *phi_in, int write, hipStream_t st) {
     (void)R;
-    hipLaunchKernelGGL(k_springs_io, dim3((total_slots + EACH_SLOTS - 1) / EACH_SLOTS), dim3(EACH_SLOTS), 0, st, robots, total_slots,
+    hipLaunchKernelGGL(k_springs_io, dim3((total_slots + EACH_SLOTS - 1) / EACH_SLOTS), dim3(EACH_THREADS), 0, st, robots, total_slots,
                        slot_robot, slot_node, ix, spring_off, pl, voxel_len, ij, L0, k, a, phi, k_in, a_in, phi_in,
                        write);
     return hipGetLastError();
