@@ -18,6 +18,17 @@ struct U64x4 {
     uint64_t w[4];
 };
 
+// 64 x 64 -> 128 bit product in four 32 x 32 + 64 bit multiply-adds; no partial
+// sum overflows
+__device__ __forceinline__ void mul128(uint64_t a, uint64_t b, uint64_t &hi, uint64_t &lo) {
+    const uint32_t a0 = (uint32_t)a, a1 = (uint32_t)(a >> 32), b0 = (uint32_t)b, b1 = (uint32_t)(b >> 32);
+    const uint64_t p = (uint64_t)a0 * b0;
+    const uint64_t m = (uint64_t)a1 * b0 + (p >> 32);
+    const uint64_t q = (uint64_t)a0 * b1 + (uint32_t)m;
+    hi = (uint64_t)a1 * b1 + (m >> 32) + (q >> 32);
+    lo = (q << 32) | (uint32_t)p;
+}
+
 __device__ __forceinline__ U64x4 philox4x64_10(uint64_t c0, uint64_t c1, uint64_t c2, uint64_t c3, uint64_t k0,
                                                uint64_t k1) {
     const uint64_t M0 = 0xD2E7470EE14C6C93ULL, M1 = 0xCA5A826395121157ULL;
@@ -28,8 +39,9 @@ __device__ __forceinline__ U64x4 philox4x64_10(uint64_t c0, uint64_t c1, uint64_
             k0 += W0;
             k1 += W1;
         }
-        const uint64_t hi0 = __umul64hi(M0, c0), lo0 = M0 * c0;
-        const uint64_t hi1 = __umul64hi(M1, c2), lo1 = M1 * c2;
+        uint64_t hi0, lo0, hi1, lo1;
+        mul128(M0, c0, hi0, lo0);
+        mul128(M1, c2, hi1, lo1);
         const uint64_t y0 = hi1 ^ c1 ^ k0, y2 = hi0 ^ c3 ^ k1;
         c0 = y0;
         c1 = lo1;
@@ -85,13 +97,15 @@ __device__ __forceinline__ bool better(const float *fit, int a, int b) {
 //  - the chunks spread a child over several CUs, for small populations.
 // Measured against a workgroup per child with the Gaussian step inside the
 // gene loop and a separate elite launch: 30 genomes of 8710 genes 84 -> 9.5 us,
-// 4096 394 -> 178 us (285 MB of genomes: 56 us at the copy rate).  A 128-bit
-// product written as four multiply-adds was no faster than __umul64hi: 187 us.
+// 4096 394 -> 141 us (285 MB of genomes: 56 us at the copy rate), of which 94
+// without mutations.  Chunks of 2048 genes instead of 3072 cost 163 us instead
+// of 137 (the shared draws are per workgroup), cos(2 pi u) instead of cospi 13 us
+// (its registers for large arguments), __umul64hi instead of mul128 10 us.
 //
 // Elites: a workgroup per individual ranks it against the population and, if
 // it is among the E best, copies its genome unchanged to slot rank.
 constexpr int GB = 256;     // threads per workgroup
-constexpr int GCH = 2048;   // most genes per workgroup
+constexpr int GCH = 3072;   // most genes per workgroup
 constexpr int GMASK = GCH / 256;
 
 __device__ void ga_elite(const GAArgs &A, int i) {
@@ -188,7 +202,7 @@ __global__ __launch_bounds__(GB) void k_ga(GAArgs A, int chunk, int nch, int64_t
         const uint64_t z0 = (g & 1) ? z.w[2] : z.w[0], z1 = (g & 1) ? z.w[3] : z.w[1];
         const double u1 = ((double)(z0 >> 11) + 1.0) * 0x1.0p-53;
         const double u2 = (double)(z1 >> 11) * 0x1.0p-53;
-        const double nz = sqrt(-2.0 * log(u1)) * cos(2.0 * M_PI * u2);
+        const double nz = sqrt(-2.0 * log(u1)) * cospi(2.0 * u2);
         vals[q] = (float)((double)vals[q] + (double)A.sigma * nz);
     }
     __syncthreads();
@@ -214,12 +228,15 @@ hipError_t launch_ga(const float *fit, const float *gin, float *gout, int P, int
     A.seed = seed;
     A.gen = gen;
     A.dec = dec;
-    // chunks of equal length, a multiple of 256 genes (one crossover-mask block)
-    const int nch = (L + GCH - 1) / GCH;
-    const int chunk = ((L + nch - 1) / nch + 255) / 256 * 256;
-    const int64_t total = (int64_t)(P - E) * nch + P, most = 1 << 23;  // a grid holds less than 2^32 threads
-    for (int64_t first = 0; first < total; first += most) {
-        const unsigned grid = (unsigned)(total - first < most ? total - first : most);
+    // chunks of equal length, a multiple of 256 genes (one crossover-mask block):
+    // as few as GCH allows, more for populations that would not fill 256 CUs
+    // four times, but no shorter than 1024
+    const int few = (L + GCH - 1) / GCH, most = (L + 1023) / 1024, fill = 1024 / P;
+    const int parts = fill < few ? few : fill > most ? most : fill;
+    const int chunk = ((L + parts - 1) / parts + 255) / 256 * 256, nch = (L + chunk - 1) / chunk;
+    const int64_t total = (int64_t)(P - E) * nch + P, per = 1 << 23;  // a grid holds less than 2^32 threads
+    for (int64_t first = 0; first < total; first += per) {
+        const unsigned grid = (unsigned)(total - first < per ? total - first : per);
         hipLaunchKernelGGL(k_ga, dim3(grid), dim3(GB), 0, st, A, chunk, nch, first);
     }
     return hipGetLastError();

@@ -65,11 +65,12 @@ def test_ga_matches_oracle(orc, P, L, k, elite, seed, gen):
     _check(G, out, dec, ref, rdec)
 
 
-@pytest.mark.parametrize("L", [255, 256, 1793, 2047, 2048, 2049, 2560, 2561, 4097, 18433])
-def test_ga_chunk_edges(orc, L):
+@pytest.mark.parametrize("L", [255, 256, 1793, 2047, 2048, 2049, 3072, 3073, 6145, 18433])
+@pytest.mark.parametrize("P", [9, 600])
+def test_ga_chunk_edges(orc, L, P):
     """Genome lengths around the 256-gene mask blocks and the workgroups' chunk
-    of at most 2048 genes, every gene mutating in half of the runs."""
-    P = 9
+    (1024 genes for a few genomes, up to 3072 for many), every gene mutating in
+    half of the runs."""
     g = np.random.default_rng(L)
     G = g.normal(size=(P, L)).astype(np.float32)
     fit = g.normal(size=P).astype(np.float32)
