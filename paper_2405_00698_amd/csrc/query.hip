@@ -386,10 +386,12 @@ hipError_t launch_query(const RobotInfo *robots, int R, uint32_t sides, const fl
     // tiles of 16 voxels per workgroup: a multiple of its 8 waves, as many as
     // still leave two workgroups for each of 256 CUs, so that the weights' way
     // into LDS is shared by many tiles (1024 uneven robots in BF16: 151 us with
-    // a workgroup per robot, 166 us with four for the largest)
+    // a workgroup per robot, 166 us with four for the largest).  When workgroups of
+    // 4 tiles still have a CU each, half their waves only stage weights and no
+    // SIMD runs two tiles in turn.
     const int maxt = (max_side * max_side * max_side + 15) / 16;
     const int64_t want = (int64_t)R * maxt / (512 * 8);
-    const int tiles = 8 * (int)(want < 1 ? 1 : want > 16 ? 16 : want);
+    const int tiles = (int64_t)R * ((maxt + 3) / 4) <= 256 ? 4 : 8 * (int)(want < 1 ? 1 : want > 16 ? 16 : want);
     const dim3 grid((maxt + tiles - 1) / tiles, R);
     if (bf)
         hipLaunchKernelGGL((table ? k_query_bf16<true> : k_query_bf16<false>), grid, dim3(QB), 0, st, robots, genomes,

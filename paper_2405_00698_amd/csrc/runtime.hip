@@ -234,6 +234,8 @@ int finish_build(sr_pop *pop) {
     pop->cur = 0;
     pop->h_step = 0;
     pop->rec_valid = pop->ck_every > 0;
+    if (!pop->h_built)
+        HIPC(pop, hipHostMalloc(reinterpret_cast<void **>(&pop->h_built), sizeof(int64_t) * (2 * (size_t)pop->R + 3)));
     HIPC(pop, launch_finish_build(pop->d_robots, pop->R, pop->bad_class, pop->d_mass_off, pop->d_spring_off,
                                   pop->d_step, pop->h_built, pop->st));
     HIPC(pop, hipStreamSynchronize(pop->st));
@@ -427,8 +429,6 @@ int pop_create(const sr_sim_params *params, int32_t n_robots, const int32_t *gri
         ALLOC(pop->q_table, query_table_bytes(pop->h_robots.data(), n_robots));
     ALLOC(pop->vox_robot, (size_t)vox);
 #undef ALLOC
-    if (e == hipSuccess)
-        e = hipHostMalloc(reinterpret_cast<void **>(&pop->h_built), sizeof(int64_t) * (2 * (size_t)n_robots + 3));
     if (e != hipSuccess) {
         pop_free(pop);
         delete pop;
