@@ -169,7 +169,8 @@ struct PersistCfg {
     int n, block, variant;
 };
 bool persist_supported(const PersistCfg &cfg, bool phase);
-int persist_default_block(int n, bool dash, bool vox, int *variant);
+// alone: the population leaves every robot a CU of its own
+int persist_default_block(int n, bool dash, bool vox, bool alone, int *variant);
 int persist_list(int n, int32_t *blocks, int32_t *variants, int cap);
 size_t persist_lds_bytes(const PersistCfg &cfg);
 hipError_t launch_persistent(const PersistCfg &cfg, bool phase, const RobotInfo *robots, const int32_t *list,

@@ -35,6 +35,7 @@ static __device__ __align__(256) float2 scratch[SR_NOALLOC_MAX_STEPS];
 
 namespace {
 constexpr int kMaxDevices = 64;
+constexpr int kCUs = 256;  // compute units of an MI355X
 constexpr int NSET = 3;  // segment buffer sets of the adjoint pipeline
 constexpr int REC_LANES = 4;  // side groups of a recorded run or a reverse sweep at once
 std::mutex g_scratch_mu;
@@ -448,7 +449,7 @@ int pop_create(const sr_sim_params *params, int32_t n_robots, const int32_t *gri
         g.offset = (int)lists.size();
         g.count = (int)kv.second.size();
         g.cfg.n = kv.first;
-        g.cfg.block = persist_default_block(kv.first, pop->dash, true, &g.cfg.variant);
+        g.cfg.block = persist_default_block(kv.first, pop->dash, true, n_robots <= kCUs, &g.cfg.variant);
         lists.insert(lists.end(), kv.second.begin(), kv.second.end());
         pop->groups.push_back(g);
     }
@@ -910,7 +911,7 @@ int pop_set_spring_params(sr_pop *pop, const float *k, const float *a, const flo
     pop->vox_ok = false;
     for (auto &g : pop->groups)
         if (g.cfg.variant & 96) {
-            g.cfg.block = persist_default_block(g.n, pop->dash, false, &g.cfg.variant);
+            g.cfg.block = persist_default_block(g.n, pop->dash, false, pop->R <= kCUs, &g.cfg.variant);
             clear_graphs(pop);
         }
     HIPC(pop, launch_springs_io(pop->d_robots, pop->R, pop->total_slots, pop->slot_robot, pop->slot_node, pop->ix,

@@ -1505,7 +1505,7 @@ const PersistEntry kPersist[] = {
     SR_PLT(10, 768, 0, 3, 3, 0, 1), SR_PLSC(10, 512, 0, 12, 3),
     SR_PLT(11, 896, 0, 2, 2, 0, 1), SR_PRUC(11, 896, 1, 1, 1, 3), SR_PVL(11, 256, 1, 2, 1, 1, 4),
     SR_PLT(12, 768, 0, 2, 2, 1, 1), SR_PRUC(12, 768, 2, 1, 1, 3),
-    SR_PLT(8, 768, 0, 3, 3, 0, 1),  // slot plan at 8^3: 3 % faster with one robot per CU, slower with two
+    SR_PLT(8, 768, 0, 3, 3, 0, 1),  // slot plan at 8^3, default with a CU per robot (kAlone8)
     // several small robots per workgroup (measured slower in the uneven population)
     SR_PLFP(4, 128, 4), SR_PLFP(5, 256, 2), SR_PLFP(6, 384, 2),
     // plain one-chunk exchange (cross-check of the pipelined forms) and the recompute variant
@@ -1603,9 +1603,15 @@ int persist_list(int n, int32_t *blocks, int32_t *variants, int cap) {
     return cnt;
 }
 
-int persist_default_block(int n, bool dash, bool vox, int *variant) {
+// A robot alone on its CU at 8^3 takes the balanced slot plan with tight rows:
+// 1000 steps of 256 robots 1595 us against 1650 to 1800 with the default, whose
+// 80 registers let two robots share a CU (2790 against 3170 us at 512).
+constexpr int kAlone8 = 1 + 256 * 3 + 4096 * 4 + 131072 + 262144 + 524288 + 1048576;
+
+int persist_default_block(int n, bool dash, bool vox, bool alone, int *variant) {
     for (const auto &e : kPersist)
-        if (e.n == n && ((e.variant & 16) != 0) == dash && (vox || !(e.variant & 96))) {
+        if (e.n == n && ((e.variant & 16) != 0) == dash && (vox || !(e.variant & 96)) &&
+            !(alone && n == 8 && !dash && e.variant != kAlone8)) {
             *variant = e.variant;
             return e.block;
         }

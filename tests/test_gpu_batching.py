@@ -163,3 +163,22 @@ def test_codesign_loop_resumes_at_a_generation_bitwise():
             assert [r[key] for r in h_a + h_b] == [r[key] for r in h_full], (g, key)
         assert torch.equal(end, full), g
     say("resume: best fitness per generation", ["%.4f" % r["fit_max"] for r in h_full])
+
+
+@pytest.mark.parametrize("robots", [256, 257])
+def test_default_kernel_at_8_by_population(robots):
+    """256 robots of 8^3 leave each a CU and take the slot plan, 257 do not;
+    the robots' states are the same bits."""
+    from paper_2405_00698_amd import api
+    above = api.persist_configs(8)[0]
+    cls, w = voxel_population([8] * 257, 67)
+    first = gpu_population([8], cls[:512], w[:512])
+    P = gpu_population([8] * robots, cls[:512 * robots], w[:512 * robots])
+    assert P.persist_variant(8) == ((768, 1983233) if robots == 256 else above)
+    first.set_persist_variant(8, *above)
+    for q in (first, P):
+        q.step(200)
+    a, b = first.state(), P.state()
+    n = a[0].shape[0]
+    assert np.array_equal(a[0].cpu().numpy(), b[0][:n].cpu().numpy())
+    assert np.array_equal(a[1].cpu().numpy(), b[1][:n].cpu().numpy())
