@@ -26,10 +26,10 @@ struct AArgs {
     int count;
     Planes pl;
     const float4 *x0;
-    const float4 *rec_x, *rec_v;  // [n_steps * slot_base + t * slots + s]
+    const float4 *rec_x, *rec_v;  // [rec_steps * slot_base + t * slots + s]
     const float4 *rec_u;          // v_n (dashpots, damped ground), same layout
     float4 *rec_l;                // lambda_F of every step (split form), same layout
-    int n_steps;
+    int n_steps, rec_steps;       // steps of this segment, steps that the buffers hold per robot
     const float2 *sc;
     float4 *lx, *lv;    // per slot
     float *gk, *gs, *gc;  // per stencil entry
@@ -126,7 +126,7 @@ __global__ __launch_bounds__(BS) void k_adjoint(AArgs A) {
         const int r = A.list[q];
         const int base = A.robots[r].slot_base;
         const int pbase = NDIR * base;
-        const size_t rbase = (size_t)A.n_steps * base;
+        const size_t rbase = (size_t)A.rec_steps * base;
         const float4 ghost = make_float4(1e4f, 1e4f, 1e4f, 0.f), zero = make_float4(0.f, 0.f, 0.f, 0.f);
         if (XCH)
             for (int i = tid; i < NR * NDC * CL; i += BS) ku[i] = 0.f;
@@ -570,7 +570,7 @@ __device__ __forceinline__ void adj_grad_robot(const AArgs &A, int q, float4 *xs
         const int r = A.list[q];
         const int base = A.robots[r].slot_base;
         const int pbase = NDIR * base;
-        const size_t rbase = (size_t)A.n_steps * base;
+        const size_t rbase = (size_t)A.rec_steps * base;
         const float4 ghost = make_float4(1e4f, 1e4f, 1e4f, 0.f), zero = make_float4(0.f, 0.f, 0.f, 0.f);
         for (int i = tid; i < PAD; i += BS) {
             xs[i] = ghost;
@@ -1144,7 +1144,7 @@ bool adjoint_is_split(int n, bool vel) {
 
 hipError_t launch_adjoint(int n, bool phase, const RobotInfo *robots, const int32_t *list, int count, Planes pl,
                           const float4 *x0, const float4 *rec_x, const float4 *rec_v, const float4 *rec_u,
-                          float4 *rec_l, int n_steps, const float2 *sc, float4 *lx, float4 *lv, float *gk, float *gs,
+                          float4 *rec_l, int n_steps, int rec_steps, const float2 *sc, float4 *lx, float4 *lv, float *gk, float *gs,
                           float *gc, float *gd, SimConst c, hipStream_t st) {
     const bool vel = c.dash || c.gdamp;  // forces that depend on the velocities
     if (vel && (!rec_u || !gd)) return hipErrorInvalidValue;
@@ -1163,6 +1163,7 @@ hipError_t launch_adjoint(int n, bool phase, const RobotInfo *robots, const int3
     A.rec_u = rec_u;
     A.rec_l = rec_l;
     A.n_steps = n_steps;
+    A.rec_steps = rec_steps;
     A.sc = sc;
     A.lx = lx;
     A.lv = lv;
@@ -1178,7 +1179,7 @@ hipError_t launch_adjoint(int n, bool phase, const RobotInfo *robots, const int3
 
 hipError_t launch_adj_grad(int n, bool phase, const RobotInfo *robots, const int32_t *list, int count, Planes pl,
                            const float4 *x0, const float4 *rec_x, const float4 *rec_u, float4 *rec_l, int n_steps,
-                           const float2 *sc, float *gk, float *gs, float *gc, float *gd, SimConst c, hipStream_t st) {
+                           int rec_steps, const float2 *sc, float *gk, float *gs, float *gc, float *gd, SimConst c, hipStream_t st) {
     const bool vel = c.dash || c.gdamp;
     if (vel && (!rec_u || !gd)) return hipErrorInvalidValue;
     const AdjEntry *e = nullptr;
@@ -1195,6 +1196,7 @@ hipError_t launch_adj_grad(int n, bool phase, const RobotInfo *robots, const int
     A.rec_u = rec_u;
     A.rec_l = rec_l;
     A.n_steps = n_steps;
+    A.rec_steps = rec_steps;
     A.sc = sc;
     A.gk = gk;
     A.gs = gs;

@@ -123,20 +123,22 @@ hipError_t launch_sincos_at(float2 *sc, int64_t step0, int n, double omega_dt, i
 
 // recording forward for the adjoint: x_n and the pre-friction velocity v'_n of
 // every step, and (rec_u not null: dashpots or a damped ground) v_n as well
-// (vox: the voxel terms match the spring planes)
+// (vox: the voxel terms match the spring planes).  A robot's records start at
+// rec_steps * slot_base whatever the segment's length, so groups on segments of
+// different lengths share a buffer without touching each other's part.
 hipError_t launch_record(int n, bool phase, bool vox, const RobotInfo *robots, const int32_t *list, int count, Planes pl,
-                         const float4 *x, const float4 *v, const float2 *sc, int n_steps, uint8_t *diverged, SimConst c,
-                         float4 *rec_x, float4 *rec_v, float4 *rec_u, hipStream_t st);
+                         const float4 *x, const float4 *v, const float2 *sc, int n_steps, int rec_steps,
+                         uint8_t *diverged, SimConst c, float4 *rec_x, float4 *rec_v, float4 *rec_u, hipStream_t st);
 // reverse step over one recorded segment; for a side whose adjoint is split
 // (adjoint_is_split), rec_l (a buffer like rec_x) takes lambda_F of every step
 // and launch_adj_grad then forms the segment's parameter-gradient sums
 bool adjoint_is_split(int n, bool vel);
 hipError_t launch_adj_grad(int n, bool phase, const RobotInfo *robots, const int32_t *list, int count, Planes pl,
                            const float4 *x0, const float4 *rec_x, const float4 *rec_u, float4 *rec_l, int n_steps,
-                           const float2 *sc, float *gk, float *gs, float *gc, float *gd, SimConst c, hipStream_t st);
+                           int rec_steps, const float2 *sc, float *gk, float *gs, float *gc, float *gd, SimConst c, hipStream_t st);
 hipError_t launch_adjoint(int n, bool phase, const RobotInfo *robots, const int32_t *list, int count, Planes pl,
                           const float4 *x0, const float4 *rec_x, const float4 *rec_v, const float4 *rec_u,
-                          float4 *rec_l, int n_steps, const float2 *sc, float4 *lx, float4 *lv, float *gk, float *gs,
+                          float4 *rec_l, int n_steps, int rec_steps, const float2 *sc, float4 *lx, float4 *lv, float *gk, float *gs,
                           float *gc, float *gd, SimConst c, hipStream_t st);
 hipError_t launch_adj_init(const RobotInfo *robots, int total_slots, const int32_t *slot_robot, const float4 *x0,
                            const float *dJ, float4 *lx, float4 *lv, float *gk, float *gs, float *gc, float *gd,

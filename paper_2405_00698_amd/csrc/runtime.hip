@@ -1100,7 +1100,7 @@ int pop_backward(sr_pop *pop, const float *dJ_dfitness, float *g_k, float *g_a, 
         // buffer set b was last read by the reversal (and gradient pass) of segment seg + NSET
         if (seg + NSET < nseg) HIPC(pop, hipStreamWaitEvent(st, done(g, b), 0));
         HIPC(pop, launch_record(gr.n, pop->phase, pop->vox_ok, pop->d_robots, pop->d_lists + gr.offset, gr.count, pop->pl,
-                                pop->ck_x + off, pop->ck_v + off, pop->adj_sc + (int64_t)seg * K, steps(seg),
+                                pop->ck_x + off, pop->ck_v + off, pop->adj_sc + (int64_t)seg * K, steps(seg), K,
                                 pop->diverged, pop->c, pop->rec_x[b], pop->rec_v[b], pop->rec_u[b], st));
         HIPC(pop, hipEventRecord(event(RECORDED, g, b), st));
         return SR_OK;
@@ -1120,7 +1120,7 @@ int pop_backward(sr_pop *pop, const float *dJ_dfitness, float *g_k, float *g_a, 
             if (seg == 0 && nseg > 1) HIPC(pop, hipStreamWaitEvent(st, event(SUMMED, g, 1), 0));
             HIPC(pop, hipStreamWaitEvent(st, event(REVERSED, g, b), 0));
             HIPC(pop, launch_adj_grad(gr.n, pop->phase, pop->d_robots, pop->d_lists + gr.offset, gr.count, pop->pl,
-                                      pop->x0, pop->rec_x[b], pop->rec_u[b], pop->rec_l[b], steps(seg),
+                                      pop->x0, pop->rec_x[b], pop->rec_u[b], pop->rec_l[b], steps(seg), K,
                                       pop->adj_sc + (int64_t)seg * K, pop->gk, pop->gs, pop->gc, pop->gd, pop->c,
                                       st));
             HIPC(pop, hipEventRecord(event(SUMMED, g, b), st));
@@ -1136,7 +1136,7 @@ int pop_backward(sr_pop *pop, const float *dJ_dfitness, float *g_k, float *g_a, 
             if (!ahead && (rc = recompute(seg, g, lane(g)))) return rc;
             HIPC(pop, hipStreamWaitEvent(lane(g), event(RECORDED, g, b), 0));
             HIPC(pop, launch_adjoint(gr.n, pop->phase, pop->d_robots, pop->d_lists + gr.offset, gr.count, pop->pl,
-                                     pop->x0, pop->rec_x[b], pop->rec_v[b], pop->rec_u[b], pop->rec_l[b], steps(seg),
+                                     pop->x0, pop->rec_x[b], pop->rec_v[b], pop->rec_u[b], pop->rec_l[b], steps(seg), K,
                                      pop->adj_sc + (int64_t)seg * K, pop->lx, pop->lv, pop->gk, pop->gs, pop->gc,
                                      pop->gd, pop->c, lane(g)));
             HIPC(pop, hipEventRecord(event(REVERSED, g, b), lane(g)));

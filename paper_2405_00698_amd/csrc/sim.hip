@@ -190,10 +190,11 @@ struct PArgs {
     // checkpoint of the state at the launch's start (null: none)
     float4 *ck_x, *ck_v;
     // recording form: per step the positions x_n and the pre-friction velocity v'_n
-    // of every slot, at rec_x[n_steps * slot_base + t * slots + s]; rec_u (when
+    // of every slot, at rec_x[rec_steps * slot_base + t * slots + s]; rec_u (when
     // not null) the velocity v_n at the start of the step.  Its end state is not
     // stored: x and v are the checkpoint it starts from.
     float4 *rec_x, *rec_v, *rec_u;
+    int rec_steps;
 };
 
 // Spring parameters rebuilt from voxels (VOX): every spring touching a lattice
@@ -1029,11 +1030,11 @@ __global__ __launch_bounds__(BS) void k_persist(PArgs A) {
                 const int s = sk[k];
                 if (pres[k]) {
                     float3 vp;
-                    if (REC) A.rec_x[(size_t)A.n_steps * base + (size_t)t * SL + s] = make_float4(xr[k].x, xr[k].y, xr[k].z, 1.f);
+                    if (REC) A.rec_x[(size_t)A.rec_steps * base + (size_t)t * SL + s] = make_float4(xr[k].x, xr[k].y, xr[k].z, 1.f);
                     if (REC && A.rec_u)
-                        A.rec_u[(size_t)A.n_steps * base + (size_t)t * SL + s] = make_float4(vr[k].x, vr[k].y, vr[k].z, 0.f);
+                        A.rec_u[(size_t)A.rec_steps * base + (size_t)t * SL + s] = make_float4(vr[k].x, vr[k].y, vr[k].z, 0.f);
                     integrate_node(c, xr[k], vr[k], Ff[k], Fb[k], REC ? &vp : nullptr);
-                    if (REC) A.rec_v[(size_t)A.n_steps * base + (size_t)t * SL + s] = make_float4(vp.x, vp.y, vp.z, 0.f);
+                    if (REC) A.rec_v[(size_t)A.rec_steps * base + (size_t)t * SL + s] = make_float4(vp.x, vp.y, vp.z, 0.f);
                     xn[PAD + s] = make_float4(xr[k].x, xr[k].y, xr[k].z, 1.f);
                     if constexpr (DASH) vb[PAD + s] = make_float4(vr[k].x, vr[k].y, vr[k].z, 0.f);
                 }
@@ -1236,7 +1237,7 @@ __global__ __launch_bounds__(BS) void k_persist_vd(PArgs A) {
             for (int k = 0; k < NPT; ++k) {
                 const int s = tid + k * BS;
                 if (!pres[k]) continue;
-                const size_t at = (size_t)A.n_steps * base + (size_t)t * SL + s;
+                const size_t at = (size_t)A.rec_steps * base + (size_t)t * SL + s;
                 float3 vp;
                 if (REC) {
                     A.rec_x[at] = make_float4(xr[k].x, xr[k].y, xr[k].z, 1.f);
@@ -1637,6 +1638,7 @@ hipError_t launch_persistent(const PersistCfg &cfg, bool phase, const RobotInfo 
     A.ck_x = ck_x;
     A.ck_v = ck_v;
     A.rec_x = nullptr;
+    A.rec_steps = 0;
     A.rec_v = nullptr;
     A.rec_u = nullptr;
     PersistFn fn = phase ? e->fn_phase : e->fn;
@@ -1645,8 +1647,8 @@ hipError_t launch_persistent(const PersistCfg &cfg, bool phase, const RobotInfo 
 }
 
 hipError_t launch_record(int n, bool phase, bool vox, const RobotInfo *robots, const int32_t *list, int count, Planes pl,
-                         const float4 *x, const float4 *v, const float2 *sc, int n_steps, uint8_t *diverged,
-                         SimConst c, float4 *rec_x, float4 *rec_v, float4 *rec_u, hipStream_t st) {
+                         const float4 *x, const float4 *v, const float2 *sc, int n_steps, int rec_steps,
+                         uint8_t *diverged, SimConst c, float4 *rec_x, float4 *rec_v, float4 *rec_u, hipStream_t st) {
     // the spring-dashpot model records with the dashpot kernels (the same bits
     // as its production kernels)
     const PersistEntry *e = nullptr;
@@ -1675,6 +1677,7 @@ hipError_t launch_record(int n, bool phase, bool vox, const RobotInfo *robots, c
     A.rec_x = rec_x;
     A.rec_v = rec_v;
     A.rec_u = rec_u;
+    A.rec_steps = rec_steps;
     hipLaunchKernelGGL(phase ? e->fn_phase : e->fn, dim3(count), dim3(e->block), 0, st, A);
     return hipGetLastError();
 }

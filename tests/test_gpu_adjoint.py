@@ -331,3 +331,33 @@ def test_adjoint_forward_time_ratio_c4():
     say("C4 forward %.4f s  backward %.4f s  ratio %.2f" % (tf, tb, tb / tf))
     assert torch.isfinite(g["k"]).all()
     assert tb / tf < 10.0
+
+
+@pytest.mark.parametrize("dash", [False, True])
+def test_group_gradients_do_not_depend_on_the_other_groups(dash):
+    """Side groups are reversed at their own pace through shared segment
+    buffers; with a last segment shorter than the others (246 = 4 * 50 + 46)
+    each group's spring gradients are the bits it has in a population alone."""
+    from paper_2405_00698_amd import table2_params
+    params = table2_params() if dash else None
+    sides = [6, 7, 8, 9] * 13
+    cls, w = voxel_population(sides, 68)
+    at = np.concatenate([[0], np.cumsum([n ** 3 for n in sides])])
+
+    def gradients(robots):
+        from paper_2405_00698_amd.api import Population
+        P = Population([sides[r] for r in robots], params=params)
+        P.build_from_voxels(torch.from_numpy(np.concatenate([cls[at[r]:at[r + 1]] for r in robots])).to(DEV),
+                            torch.from_numpy(np.concatenate([w[at[r]:at[r + 1]] for r in robots])).to(DEV))
+        P.record(50, 246)
+        P.step(246)
+        out = [g.cpu().numpy() for g in P.backward(torch.ones(len(robots), device=DEV)).values()]
+        off = np.concatenate([[0], np.cumsum(P.counts()[1])])
+        return {r: [g[off[i]:off[i + 1]] for g in out] for i, r in enumerate(robots)}
+
+    together = gradients(list(range(len(sides))))
+    for n in (6, 7, 8, 9):
+        alone = gradients([r for r in range(len(sides)) if sides[r] == n])
+        for r, g in alone.items():
+            for a, b in zip(g, together[r]):
+                assert np.array_equal(a, b), (n, r)
