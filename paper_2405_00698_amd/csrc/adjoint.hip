@@ -19,6 +19,7 @@
 namespace sr {
 
 namespace {
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 struct AArgs {
     const RobotInfo *robots;
@@ -29,7 +30,7 @@ struct AArgs {
     const float4 *rec_x, *rec_v;  // [rec_steps * slot_base + t * slots + s]
     const float4 *rec_u;          // v_n (dashpots, damped ground), same layout
     float4 *rec_l;                // lambda_F of every step (split form), same layout
-    int n_steps, rec_steps;       // steps of this segment, steps that the buffers hold per robot
+    int n_steps, rec_steps;       // this segment's steps, the steps a buffer holds for each robot
     const float2 *sc;
     float4 *lx, *lv;    // per slot
     float *gk, *gs, *gc;  // per stencil entry
@@ -93,7 +94,7 @@ __device__ __forceinline__ void spring_grad_sums(float r2, float ir, float kL, f
 // form from 10^3 on, without (two or three planes) only at 12^3: at 10^3 and
 // 11^3 the held parameters spill 0 to 33 registers, and the extra reads cost
 // more (11^3, 256 robots: 9.6 ms a backward of 400 steps held, 10.3 read).
-// Together with the gradient pass in four parts: backward of 400 steps, Table II
+// Together with a gradient pass without spills: backward of 400 steps, Table II
 // model, 64 robots of 10^3 / 11^3 / 12^3 7.6 / 13.6 / 27.6 -> 6.1 / 7.8 / 12.8 ms,
 // 256 robots 17.0 / 33.6 / 63.2 -> 13.2 / 21.2 / 27.7 ms (12^3 with the recording
 // kernel of its own); without dashpots 256 of 12^3 16.4 -> 15.4 ms.
@@ -552,6 +553,29 @@ __global__ __launch_bounds__(BS) void k_adjoint(AArgs A) {
     }
 }
 
+// One forward spring of the split gradient pass at one step: self (X, lambda_F L,
+// velocity V) is the lower end, (Y, LJ, VJ) the upper; with dashpots also dJ/dc,
+// as in the fused reverse step.
+template <bool PHASE, bool DASH>
+__device__ __forceinline__ void grad_spring(float3 X, float3 L, float3 V, float3 Y, float3 LJ, float3 VJ, float L0,
+                                            float pk, float pa, float pb, float pik, float2 sct, float &gk, float &gs,
+                                            float &gc, float &gd) {
+    const float dx = Y.x - X.x, dy = Y.y - X.y, dz = Y.z - X.z;
+    const float ux = LJ.x - L.x, uy = LJ.y - L.y, uz = LJ.z - L.z;
+    const float r2 = len2(dx, dy, dz);
+    const float ir = __builtin_amdgcn_rsqf(r2);
+    float kL = fmaf(pa, sct.x, pk * L0);
+    if (PHASE) kL = fmaf(pb, sct.y, kL);
+    const float du = fmaf(dz, uz, fmaf(dy, uy, dx * ux));
+    spring_grad_sums(r2, ir, kL, du, pk, pik, sct, gk, gs, gc);
+    if constexpr (DASH) {
+        const float wx = VJ.x - V.x, wy = VJ.y - V.y, wz = VJ.z - V.z;
+        const float ir2 = ir * ir;
+        const float wv = fmaf(dz, wz, fmaf(dy, wy, dx * wx));
+        gd = fmaf(-wv * du, ir2, gd);
+    }
+}
+
 // Split form, second pass: the parameter-gradient sums of the forward springs
 // of directions D0 .. D1 - 1 over one segment, from the recorded positions x_t
 // (rec_x; an absent slot sits at its build position) and the reverse step's
@@ -661,25 +685,13 @@ __device__ __forceinline__ void adj_grad_robot(const AArgs &A, int q, float4 *xs
 #pragma unroll
                 for (int j = 0; j < ND; ++j) {
                     const int d = D0 + j;
-                    const float3 Y = ld3(xs + s + (PAD + dir_off(d, N)));
-                    const float3 LJ = ld3(lf + s + (PAD + dir_off(d, N)));
-                    const float dx = Y.x - Xr[k].x, dy = Y.y - Xr[k].y, dz = Y.z - Xr[k].z;
-                    const float ux = LJ.x - LF[k].x, uy = LJ.y - LF[k].y, uz = LJ.z - LF[k].z;
-                    const float r2 = len2(dx, dy, dz);
-                    const float ir = __builtin_amdgcn_rsqf(r2);
-                    float kL = fmaf(pa[k][j], sct.x, pk[k][j] * L0d(c, d));
-                    if (PHASE) kL = fmaf(pb[k][j], sct.y, kL);
-                    const float du = fmaf(dz, uz, fmaf(dy, uy, dx * ux));
-                    spring_grad_sums(r2, ir, kL, du, pk[k][j], pik[k][j], sct, gk[k][j], gs[k][j], gc[k][j]);
-                    if constexpr (DASH) {
-                        // dJ/dc of the dashpot beside the spring, as in the fused reverse step
-                        const float3 VJ = ld3(vs + s + (PAD + dir_off(d, N)));
-                        const float3 VI = Vr[DASH ? k : 0];
-                        const float wx = VJ.x - VI.x, wy = VJ.y - VI.y, wz = VJ.z - VI.z;
-                        const float ir2 = ir * ir;
-                        const float wv = fmaf(dz, wz, fmaf(dy, wy, dx * wx));
-                        gd[k][DASH ? j : 0] = fmaf(-wv * du, ir2, gd[k][DASH ? j : 0]);
-                    }
+                    const int at = s + PAD + dir_off(d, N);
+                    float3 V = Xr[k], VJ = Xr[k];  // unused without dashpots
+                    if constexpr (DASH) V = Vr[DASH ? k : 0], VJ = ld3(vs + at);
+                    float none = 0.f;
+                    grad_spring<PHASE, DASH>(Xr[k], LF[k], V, ld3(xs + at), ld3(lf + at), VJ, L0d(c, d), pk[k][j],
+                                             pa[k][j], pb[k][j], pik[k][j], sct, gk[k][j], gs[k][j], gc[k][j],
+                                             DASH ? gd[k][DASH ? j : 0] : none);
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
@@ -702,11 +714,9 @@ __device__ __forceinline__ void adj_grad_robot(const AArgs &A, int q, float4 *xs
 }
 
 // The gradient pass over all directions in one workgroup per robot (PARTS 1),
-// or over 0..6 and 7..12 in two (PARTS 2), or over 0..3, 4..6, 7..9 and 10..12
-// in four side by side (blockIdx.y; they write disjoint sums).  The parts are
-// what a thread's slots hold in registers: with two parts the 2 or 3 slots of a
-// thread at 10^3-12^3 spilled 100 to 430 registers (12^3 with dashpots: 11.5 us
-// a step, in four parts GRAD4 us).
+// or over 0..6 and 7..12 in two side by side (PARTS 2; they write disjoint sums).
+// It runs beside the next segment's reversal, whose workgroups take a whole CU
+// each: few workgroups that fill a CU leave it the others.
 // DASH: also dJ/dc of the spring dashpots, from the recorded velocities v_n.
 template <int N, int BS, bool PHASE, int PARTS, bool DASH = false>
 __global__ __launch_bounds__(BS) void k_adj_grad(AArgs A) {
@@ -716,21 +726,140 @@ __global__ __launch_bounds__(BS) void k_adj_grad(AArgs A) {
     for (int q = blockIdx.x; q < A.count; q += gridDim.x) {
         if constexpr (PARTS == 1) {
             adj_grad_robot<N, BS, PHASE, 0, 13, DASH>(A, q, xs, lf, vs);
-        } else if constexpr (PARTS == 2) {
+        } else {
             if (blockIdx.y == 0)
                 adj_grad_robot<N, BS, PHASE, 0, 7, DASH>(A, q, xs, lf, vs);
             else
                 adj_grad_robot<N, BS, PHASE, 7, 13, DASH>(A, q, xs, lf, vs);
-        } else {
-            if (blockIdx.y == 0)
-                adj_grad_robot<N, BS, PHASE, 0, 4, DASH>(A, q, xs, lf, vs);
-            else if (blockIdx.y == 1)
-                adj_grad_robot<N, BS, PHASE, 4, 7, DASH>(A, q, xs, lf, vs);
-            else if (blockIdx.y == 2)
-                adj_grad_robot<N, BS, PHASE, 7, 10, DASH>(A, q, xs, lf, vs);
-            else
-                adj_grad_robot<N, BS, PHASE, 10, 13, DASH>(A, q, xs, lf, vs);
         }
+    }
+}
+
+// The same sums in tiles of TS slots.  A spring's sums need only its two ends,
+// and it is summed at its lower end, whose neighbours lie at higher slots: a
+// workgroup takes TS consecutive slots, one a thread with all 13 directions, and
+// stages them with the PAD slots above for each step (two buffers, one barrier a
+// step, the next step's values in flight over the spring work).  Bound by the
+// chain of a step in few waves (1.6 us a step in a small launch at any side, 2.2
+// with dashpots) against 2.4 to 5.5 for the form above; the workgroups are
+// numbered so that a robot's tiles share an XCD and its L2.  It is taken for the
+// segment reversed last, whose pass has nothing beside it and ends the backward
+// (64 robots, base model, 8^3 / 10^3: 242 / 294 -> 178 / 195 us of 100 steps; not at
+// 8^3 with dashpots, 212 us in two parts against 219 at 3 robots), and
+// for every segment at 12^3 and at 11^3 with dashpots (the whole backward of 256
+// robots of 12^3 15.5 -> 11.8 ms, with dashpots 27.6 -> 22.5).  On smaller sides the
+// many small workgroups beside a reversal leave its next launch no empty CU (10^3,
+// 64 and 128 robots: 3.07 and 4.2 ms with the form above, 3.3 and 4.1 in tiles).
+template <int N, int TS, bool PHASE, bool DASH>
+__global__ __launch_bounds__(TS, 2) void k_adj_grad_tiles(AArgs A) {
+    using G = Geo<N>;
+    constexpr int SL = G::SL, PAD = G::PAD, TL = TS + PAD;
+    constexpr int NT = (SL + TS - 1) / TS, NE = (TL + TS - 1) / TS;
+    __shared__ float4 xs[2][TL + 1], lf[2][TL + 1], vs[DASH ? 2 : 1][DASH ? TL + 1 : 1];
+    const int tid = threadIdx.x, T = A.n_steps;
+    const SimConst c = A.c;
+    if (T <= 0) return;
+    const int b = blockIdx.x / 8, q = b / NT * 8 + blockIdx.x % 8, s0 = b % NT * TS;
+    if (q >= A.count) return;
+    const int base = A.robots[A.list[q]].slot_base;
+    const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+    // Absent nodes rest at their places with no adjoint and ghosts lie far off:
+    // both are written once, and their steps' values go to the entry past the
+    // tile's, so that every thread has the same loads in flight.
+    int to[NE], from[NE];
+    bool pres = false;
+#pragma unroll
+    for (int e = 0; e < NE; ++e) {
+        const int i = tid + e * TS, s = s0 + i;
+        const bool in = i < TL && s < SL;
+        float4 P0 = make_float4(1e4f, 1e4f, 1e4f, 0.f);
+        if (in) P0 = A.x0[base + s];
+        to[e] = P0.w != 0.f ? i : TL;
+        from[e] = in ? s : s0;
+        if (e == 0) pres = P0.w != 0.f;
+        P0.w = 0.f;
+        if (i < TL)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                xs[h][i] = P0;
+                lf[h][i] = zero;
+                if constexpr (DASH) vs[h][i] = zero;
+            }
+    }
+    if (!__syncthreads_or(pres)) return;
+    const int pbase = NDIR * base + s0 + tid;
+    float pk[NDIR], pa[NDIR], pb[NDIR], pik[NDIR], gk[NDIR], gs[NDIR], gc[NDIR], gd[DASH ? NDIR : 1];
+#pragma unroll
+    for (int d = 0; d < NDIR; ++d) {
+        const int pi = pbase + d * SL;
+        pk[d] = pres ? A.pl.k[pi] : 0.f;
+        pa[d] = pres ? A.pl.kal[pi] : 0.f;
+        pb[d] = pres && PHASE ? A.pl.kbe[pi] : 0.f;
+        pik[d] = pk[d] != 0.f ? 1.0f / pk[d] : 0.f;
+        gk[d] = pres ? A.gk[pi] : 0.f;
+        gs[d] = pres ? A.gs[pi] : 0.f;
+        gc[d] = pres ? A.gc[pi] : 0.f;
+        if constexpr (DASH) gd[d] = pres ? A.gd[pi] : 0.f;
+    }
+    f32x4 xn[NE], ln[NE], vn[DASH ? NE : 1];
+    const size_t rbase = (size_t)A.rec_steps * base;
+    auto fetch = [&](int t) {
+        const size_t at = rbase + (size_t)t * SL;
+#pragma unroll
+        for (int e = 0; e < NE; ++e) {
+            xn[e] = *(const f32x4 *)&A.rec_x[at + from[e]];
+            ln[e] = *(const f32x4 *)&A.rec_l[at + from[e]];
+            if constexpr (DASH) vn[e] = *(const f32x4 *)&A.rec_u[at + from[e]];
+        }
+    };
+    auto stage = [&](int t) {
+#pragma unroll
+        for (int e = 0; e < NE; ++e) {
+            *(f32x4 *)&xs[t & 1][to[e]] = xn[e];
+            *(f32x4 *)&lf[t & 1][to[e]] = ln[e];
+            if constexpr (DASH) *(f32x4 *)&vs[t & 1][to[e]] = vn[e];
+        }
+    };
+    fetch(T - 1);
+    stage(T - 1);
+    fetch(T > 1 ? T - 2 : 0);
+    __syncthreads();
+    for (int t = T - 1; t >= 0; --t) {
+        const float2 sct = A.sc[t];
+        if (pres) {
+            const float4 *xb = xs[t & 1] + tid, *lb = lf[t & 1] + tid, *vb = vs[DASH ? t & 1 : 0] + (DASH ? tid : 0);
+            const float3 X = ld3(xb), L = ld3(lb), V = DASH ? ld3(vb) : X;
+            // the reads of direction d + 1 are issued before direction d's arithmetic
+            float3 Y = ld3(xb + dir_off(0, N)), LJ = ld3(lb + dir_off(0, N)), VJ = V;
+            if constexpr (DASH) VJ = ld3(vb + dir_off(0, N));
+#pragma unroll
+            for (int d = 0; d < NDIR; ++d) {
+                const float3 Yd = Y, Ld = LJ, Vd = VJ;
+                if (d + 1 < NDIR) {
+                    Y = ld3(xb + dir_off(d + 1, N));
+                    LJ = ld3(lb + dir_off(d + 1, N));
+                    if constexpr (DASH) VJ = ld3(vb + dir_off(d + 1, N));
+                }
+                float none = 0.f;
+                grad_spring<PHASE, DASH>(X, L, V, Yd, Ld, Vd, L0d(c, d), pk[d], pa[d], pb[d], pik[d], sct, gk[d],
+                                         gs[d], gc[d], DASH ? gd[DASH ? d : 0] : none);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        if (t > 0) {
+            stage(t - 1);
+            fetch(t > 1 ? t - 2 : 0);
+        }
+        __syncthreads();
+    }
+    if (!pres) return;
+#pragma unroll
+    for (int d = 0; d < NDIR; ++d) {
+        const int pi = pbase + d * SL;
+        A.gk[pi] = gk[d];
+        A.gs[pi] = gs[d];
+        A.gc[pi] = gc[d];
+        if constexpr (DASH) A.gd[pi] = gd[d];
     }
 }
 
@@ -878,7 +1007,6 @@ __global__ void k_adj_dw(DwArgs A) {
 // loops over LDS, 30 uneven robots: 1274 -> 439 us (the 12^3 robots' 14 tiles in a row).
 constexpr int OFF_W1 = 0, OFF_B1 = 4096, OFF_W2 = 4160, OFF_B2 = 8256, OFF_W3 = 8320, OFF_B3 = 8704;
 constexpr int MBT = 512, MBV = 16 * (MBT / 64), MROW = 72;
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // sum over the 16 lanes of a lane quarter, on every one of them (swaps within a
 // quad, across the half row, across the row)
@@ -1075,12 +1203,14 @@ __global__ __launch_bounds__(MBT) void k_mlp_backward(const RobotInfo *robots, c
 }
 
 typedef void (*AdjFn)(AArgs);
+constexpr int GRAD_TILE = 256;
 struct AdjEntry {
     int n, block;
     AdjFn fn, fn_phase;
-    // split form: fn is the reverse step without gradient sums, and the
-    // gradient pass g0 runs gblock threads per workgroup on a grid of robots
-    // x gy (parts of the directions in workgroups side by side)
+    // split form: fn is the reverse step without gradient sums, gt (or null) the
+    // gradient pass in tiles of GRAD_TILE slots, and g0 (or null: gt) the one
+    // beside a reversal, gblock threads per workgroup on a grid of robots x gy
+    AdjFn gt = nullptr, gt_phase = nullptr;
     int gblock = 0;
     AdjFn g0 = nullptr, g0_phase = nullptr;
     int gy = 1;
@@ -1089,26 +1219,32 @@ struct AdjEntry {
     { NN, BS, k_adjoint<NN + 1, BS, false, X>, k_adjoint<NN + 1, BS, true, X> }
 #define SR_AEL(NN, BS, LG) \
     { NN, BS, k_adjoint<NN + 1, BS, false, true, LG>, k_adjoint<NN + 1, BS, true, true, LG> }
+#define SR_GT(NN, DASH) \
+    k_adj_grad_tiles<NN + 1, GRAD_TILE, false, DASH>, k_adj_grad_tiles<NN + 1, GRAD_TILE, true, DASH>
 // split exchange form with a one-launch gradient pass
 #define SR_AESL(NN, BS, LG, GBS)                                                                                \
     {                                                                                                          \
         NN, BS, k_adjoint<NN + 1, BS, false, true, LG, false, false, false, true>,                              \
-            k_adjoint<NN + 1, BS, true, true, LG, false, false, false, true>, GBS,                              \
+            k_adjoint<NN + 1, BS, true, true, LG, false, false, false, true>, SR_GT(NN, false), GBS,             \
             k_adj_grad<NN + 1, GBS, false, 1>, k_adj_grad<NN + 1, GBS, true, 1>                                  \
     }
 // split exchange form in XC direction chunks (one chunk's rows in LDS at a
-// time), parameters per chunk with GP, the gradient pass in GY workgroups per
-// robot
-#define SR_AESC(NN, BS, LG, XC, GP, GBS, GY)                                                                    \
+// time), parameters per chunk with GP; SR_AESCG: the gradient pass beside a
+// reversal in GY workgroups per robot
+#define SR_AESC_(NN, BS, LG, XC, GP)                                                                           \
+    NN, BS, k_adjoint<NN + 1, BS, false, true, LG, false, false, false, true, XC, GP>,                          \
+        k_adjoint<NN + 1, BS, true, true, LG, false, false, false, true, XC, GP>, SR_GT(NN, false)
+#define SR_AESC(NN, BS, LG, XC, GP) \
+    { SR_AESC_(NN, BS, LG, XC, GP) }
+#define SR_AESCG(NN, BS, LG, XC, GP, GBS, GY)                                                                  \
     {                                                                                                          \
-        NN, BS, k_adjoint<NN + 1, BS, false, true, LG, false, false, false, true, XC, GP>,                      \
-            k_adjoint<NN + 1, BS, true, true, LG, false, false, false, true, XC, GP>, GBS,                      \
-            k_adj_grad<NN + 1, GBS, false, GY>, k_adj_grad<NN + 1, GBS, true, GY>, GY                            \
+        SR_AESC_(NN, BS, LG, XC, GP), GBS, k_adj_grad<NN + 1, GBS, false, GY>,                                  \
+            k_adj_grad<NN + 1, GBS, true, GY>, GY                                                               \
     }
 const AdjEntry kAdj[] = {SR_AE(1, 64, true),    SR_AE(2, 64, true),    SR_AE(3, 64, true),   SR_AEL(4, 128, 2),
                          SR_AEL(5, 256, 2),     SR_AEL(6, 384, 2),     SR_AEL(7, 512, 2),    SR_AESL(8, 768, 2, 768),
-                         SR_AESC(9, 1024, 2, 2, false, 1024, 1), SR_AESC(10, 768, 2, 3, false, 704, 2),
-                         SR_AESC(11, 1024, 0, 4, false, 1024, 2), SR_AESC(12, 768, 0, 7, true, 768, 4)};
+                         SR_AESCG(9, 1024, 2, 2, false, 1024, 1), SR_AESCG(10, 768, 2, 3, false, 704, 2),
+                         SR_AESCG(11, 1024, 0, 4, false, 1024, 2), SR_AESC(12, 768, 0, 7, true)};
 // spring dashpots or the damped ground (Table II model): the one-buffer
 // recompute form with the velocity terms
 #define SR_AED(NN, BS) \
@@ -1121,31 +1257,37 @@ const AdjEntry kAdj[] = {SR_AE(1, 64, true),    SR_AE(2, 64, true),    SR_AE(3, 
             k_adjoint<NN + 1, BS, true, true, 0, false, true, false, false, XC>                                 \
     }
 // split form of the above: the reverse recursion alone, then the gradient
-// pass with the dashpot terms in GY workgroups per robot
-#define SR_AEDS(NN, BS, XC, GP, GBS, GY)                                                                       \
+// pass with the dashpot terms
+#define SR_AEDS_(NN, BS, XC, GP, ...)                                                                          \
+    NN, BS, k_adjoint<NN + 1, BS, false, true, 0, false, true, false, true, XC, GP>,                            \
+        k_adjoint<NN + 1, BS, true, true, 0, false, true, false, true, XC, GP>, __VA_ARGS__
+#define SR_AEDS(NN, BS, XC, GP) \
+    { SR_AEDS_(NN, BS, XC, GP, SR_GT(NN, true)) }
+// last: SR_GT, or two nulls where the pass in GY workgroups is never slower
+#define SR_AEDSG(NN, BS, XC, GP, GBS, GY, ...)                                                                 \
     {                                                                                                          \
-        NN, BS, k_adjoint<NN + 1, BS, false, true, 0, false, true, false, true, XC, GP>,                        \
-            k_adjoint<NN + 1, BS, true, true, 0, false, true, false, true, XC, GP>, GBS,                        \
-            k_adj_grad<NN + 1, GBS, false, GY, true>, k_adj_grad<NN + 1, GBS, true, GY, true>, GY                \
+        SR_AEDS_(NN, BS, XC, GP, __VA_ARGS__), GBS, k_adj_grad<NN + 1, GBS, false, GY, true>,                                \
+            k_adj_grad<NN + 1, GBS, true, GY, true>, GY                                                         \
     }
 const AdjEntry kAdjD[] = {SR_AED(1, 64),        SR_AED(2, 64),        SR_AED(3, 64),        SR_AEDX(4, 128, 1),
                           SR_AEDX(5, 256, 1),   SR_AEDX(6, 384, 1),   SR_AEDX(7, 512, 1),
-                          SR_AEDS(8, 768, 2, false, 768, 2), SR_AEDS(9, 1024, 3, false, 1024, 2),
-                          SR_AEDS(10, 768, 5, true, 768, 2), SR_AEDS(11, 1024, 7, true, 1024, 4),
-                          SR_AEDS(12, 768, 13, true, 768, 4)};
+                          SR_AEDSG(8, 768, 2, false, 768, 2, nullptr, nullptr),
+                          SR_AEDSG(9, 1024, 3, false, 1024, 2, SR_GT(9, true)),
+                          SR_AEDSG(10, 768, 5, true, 768, 2, SR_GT(10, true)), SR_AEDS(11, 1024, 7, true),
+                          SR_AEDS(12, 768, 13, true)};
 
 }  // namespace
 
 bool adjoint_is_split(int n, bool vel) {
     for (const auto &q : (vel ? kAdjD : kAdj))
-        if (q.n == n) return q.g0 != nullptr;
+        if (q.n == n) return q.gt || q.g0;
     return false;
 }
 
 hipError_t launch_adjoint(int n, bool phase, const RobotInfo *robots, const int32_t *list, int count, Planes pl,
                           const float4 *x0, const float4 *rec_x, const float4 *rec_v, const float4 *rec_u,
-                          float4 *rec_l, int n_steps, int rec_steps, const float2 *sc, float4 *lx, float4 *lv, float *gk, float *gs,
-                          float *gc, float *gd, SimConst c, hipStream_t st) {
+                          float4 *rec_l, int n_steps, int rec_steps, const float2 *sc, float4 *lx, float4 *lv,
+                          float *gk, float *gs, float *gc, float *gd, SimConst c, hipStream_t st) {
     const bool vel = c.dash || c.gdamp;  // forces that depend on the velocities
     if (vel && (!rec_u || !gd)) return hipErrorInvalidValue;
     const AdjEntry *e = nullptr;
@@ -1172,20 +1314,21 @@ hipError_t launch_adjoint(int n, bool phase, const RobotInfo *robots, const int3
     A.gc = gc;
     A.gd = gd;
     A.c = c;
-    if (e->g0 && !rec_l) return hipErrorInvalidValue;
+    if ((e->gt || e->g0) && !rec_l) return hipErrorInvalidValue;
     hipLaunchKernelGGL(phase ? e->fn_phase : e->fn, dim3(count), dim3(e->block), 0, st, A);
     return hipGetLastError();
 }
 
 hipError_t launch_adj_grad(int n, bool phase, const RobotInfo *robots, const int32_t *list, int count, Planes pl,
                            const float4 *x0, const float4 *rec_x, const float4 *rec_u, float4 *rec_l, int n_steps,
-                           int rec_steps, const float2 *sc, float *gk, float *gs, float *gc, float *gd, SimConst c, hipStream_t st) {
+                           int rec_steps, const float2 *sc, float *gk, float *gs, float *gc, float *gd, SimConst c,
+                           bool beside, hipStream_t st) {
     const bool vel = c.dash || c.gdamp;
     if (vel && (!rec_u || !gd)) return hipErrorInvalidValue;
     const AdjEntry *e = nullptr;
     for (const auto &q : (vel ? kAdjD : kAdj))
         if (q.n == n) e = &q;
-    if (!e || !e->g0 || !rec_l) return hipErrorInvalidValue;
+    if (!e || !(e->gt || e->g0) || !rec_l) return hipErrorInvalidValue;
     AArgs A = {};
     A.robots = robots;
     A.list = list;
@@ -1203,7 +1346,12 @@ hipError_t launch_adj_grad(int n, bool phase, const RobotInfo *robots, const int
     A.gc = gc;
     A.gd = gd;
     A.c = c;
-    hipLaunchKernelGGL(phase ? e->g0_phase : e->g0, dim3(count, e->gy), dim3(e->gblock), 0, st, A);
+    if (e->g0 && (beside || !e->gt)) {
+        hipLaunchKernelGGL(phase ? e->g0_phase : e->g0, dim3(count, e->gy), dim3(e->gblock), 0, st, A);
+    } else {
+        const int slots = (n + 1) * (n + 1) * (n + 1), tiles = (slots + GRAD_TILE - 1) / GRAD_TILE;
+        hipLaunchKernelGGL(phase ? e->gt_phase : e->gt, dim3((count + 7) / 8 * 8 * tiles), dim3(GRAD_TILE), 0, st, A);
+    }
     return hipGetLastError();
 }
 

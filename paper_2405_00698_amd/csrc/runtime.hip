@@ -472,7 +472,7 @@ int pop_create(const sr_sim_params *params, int32_t n_robots, const int32_t *gri
     {
         const int G = (int)pop->groups.size();
         static const double chain[SR_MAX_SIDE + 1] = {0, 5.5, 5.5, 5.5, 5.5, 5.5, 5.7, 5.9, 7.9, 10, 16, 20, 31};
-        static const double sums[SR_MAX_SIDE + 1] = {0, 0, 0, 0, 0, 0, 0, 0, 2, 2, 2.4, 4.5, 5.4};
+        static const double sums[SR_MAX_SIDE + 1] = {0, 0, 0, 0, 0, 0, 0, 0, 2.2, 2.1, 2.4, 2.4, 2.4};
         auto turns = [&](int g) { return (pop->groups[g].count + 255) / 256; };
         auto cost = [&](int g) { return chain[pop->groups[g].n] * turns(g); };
         double load[REC_LANES] = {};
@@ -1110,19 +1110,22 @@ int pop_backward(sr_pop *pop, const float *dJ_dfitness, float *g_k, float *g_a, 
             if (ahead && (rc = recompute(seg, g, pop->rec_st[G]))) return rc;
         return SR_OK;
     };
+    int last[REC_LANES];  // the group that each lane reverses last
+    for (int g : pop->rec_order) last[pop->rec_lane[g]] = g;
     auto sums = [&](int seg) -> int {
         const int b = seg % NSET;
         for (int g : pop->rec_order) {
             if (!split(g)) continue;
             const SideGroup &gr = pop->groups[g];
-            // the first segment's passes, the last to run, each on its group's own lane
-            hipStream_t st = seg == 0 ? lane(g) : sum_st;
+            // the first segment's passes are the last to run: on the group's own
+            // lane where nothing follows the group there
+            hipStream_t st = seg == 0 && last[pop->rec_lane[g]] == g ? lane(g) : sum_st;
             if (seg == 0 && nseg > 1) HIPC(pop, hipStreamWaitEvent(st, event(SUMMED, g, 1), 0));
             HIPC(pop, hipStreamWaitEvent(st, event(REVERSED, g, b), 0));
             HIPC(pop, launch_adj_grad(gr.n, pop->phase, pop->d_robots, pop->d_lists + gr.offset, gr.count, pop->pl,
                                       pop->x0, pop->rec_x[b], pop->rec_u[b], pop->rec_l[b], steps(seg), K,
                                       pop->adj_sc + (int64_t)seg * K, pop->gk, pop->gs, pop->gc, pop->gd, pop->c,
-                                      st));
+                                      seg > 0, st));
             HIPC(pop, hipEventRecord(event(SUMMED, g, b), st));
         }
         return SR_OK;

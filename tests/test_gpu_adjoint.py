@@ -361,3 +361,27 @@ def test_group_gradients_do_not_depend_on_the_other_groups(dash):
         for r, g in alone.items():
             for a, b in zip(g, together[r]):
                 assert np.array_equal(a, b), (n, r)
+
+
+@pytest.mark.parametrize("dash", [False, True])
+@pytest.mark.parametrize("n", [8, 9, 10, 11, 12])
+def test_gradient_pass_forms_give_the_same_bits(n, dash):
+    """One segment is summed in tiles of 256 slots; of several, all but the one
+    reversed last by the pass beside the reversal (where the side has one).
+    Nine robots: a full and a nearly empty row of the tiles' XCD numbering."""
+    from paper_2405_00698_amd import table2_params
+    from paper_2405_00698_amd.api import Population
+    sides = [n] * 9
+    cls, w = voxel_population(sides, 69, p_empty=0.3)
+    ref = None
+    for K in (61, 20, 1):
+        P = Population(sides, params=table2_params() if dash else None)
+        P.build_from_voxels(torch.from_numpy(cls).to(DEV), torch.from_numpy(w).to(DEV))
+        P.record(K, 61)
+        P.step(61)
+        g = [q.cpu().numpy() for q in P.backward(torch.ones(9, device=DEV)).values()]
+        if ref is None:
+            ref = g
+        else:
+            for a, b in zip(g, ref):
+                assert np.array_equal(a, b), K
