@@ -746,8 +746,9 @@ __global__ __launch_bounds__(BS) void k_adj_grad(AArgs A) {
 // segment reversed last, whose pass has nothing beside it and ends the backward
 // (64 robots, base model, 8^3 / 10^3: 242 / 294 -> 178 / 195 us of 100 steps; not at
 // 8^3 with dashpots, 212 us in two parts against 219 at 3 robots), and
-// for every segment at 12^3 and at 11^3 with dashpots (the whole backward of 256
-// robots of 12^3 15.5 -> 11.8 ms, with dashpots 27.6 -> 22.5).  On smaller sides the
+// for every segment at 12^3 and at 11^3 with dashpots (1200 steps backward, 256
+// robots of 12^3 45 -> 34 ms, with dashpots 82 -> 68; 64 robots 17.1 -> 15.0 and
+// 36.9 -> 34.4).  On smaller sides the
 // many small workgroups beside a reversal leave its next launch no empty CU (10^3,
 // 64 and 128 robots: 3.07 and 4.2 ms with the form above, 3.3 and 4.1 in tiles).
 template <int N, int TS, bool PHASE, bool DASH>
@@ -759,107 +760,109 @@ __global__ __launch_bounds__(TS, 2) void k_adj_grad_tiles(AArgs A) {
     const int tid = threadIdx.x, T = A.n_steps;
     const SimConst c = A.c;
     if (T <= 0) return;
-    const int b = blockIdx.x / 8, q = b / NT * 8 + blockIdx.x % 8, s0 = b % NT * TS;
-    if (q >= A.count) return;
-    const int base = A.robots[A.list[q]].slot_base;
-    const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
-    // Absent nodes rest at their places with no adjoint and ghosts lie far off:
-    // both are written once, and their steps' values go to the entry past the
-    // tile's, so that every thread has the same loads in flight.
-    int to[NE], from[NE];
-    bool pres = false;
-#pragma unroll
-    for (int e = 0; e < NE; ++e) {
-        const int i = tid + e * TS, s = s0 + i;
-        const bool in = i < TL && s < SL;
-        float4 P0 = make_float4(1e4f, 1e4f, 1e4f, 0.f);
-        if (in) P0 = A.x0[base + s];
-        to[e] = P0.w != 0.f ? i : TL;
-        from[e] = in ? s : s0;
-        if (e == 0) pres = P0.w != 0.f;
-        P0.w = 0.f;
-        if (i < TL)
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                xs[h][i] = P0;
-                lf[h][i] = zero;
-                if constexpr (DASH) vs[h][i] = zero;
-            }
-    }
-    if (!__syncthreads_or(pres)) return;
-    const int pbase = NDIR * base + s0 + tid;
-    float pk[NDIR], pa[NDIR], pb[NDIR], pik[NDIR], gk[NDIR], gs[NDIR], gc[NDIR], gd[DASH ? NDIR : 1];
-#pragma unroll
-    for (int d = 0; d < NDIR; ++d) {
-        const int pi = pbase + d * SL;
-        pk[d] = pres ? A.pl.k[pi] : 0.f;
-        pa[d] = pres ? A.pl.kal[pi] : 0.f;
-        pb[d] = pres && PHASE ? A.pl.kbe[pi] : 0.f;
-        pik[d] = pk[d] != 0.f ? 1.0f / pk[d] : 0.f;
-        gk[d] = pres ? A.gk[pi] : 0.f;
-        gs[d] = pres ? A.gs[pi] : 0.f;
-        gc[d] = pres ? A.gc[pi] : 0.f;
-        if constexpr (DASH) gd[d] = pres ? A.gd[pi] : 0.f;
-    }
-    f32x4 xn[NE], ln[NE], vn[DASH ? NE : 1];
-    const size_t rbase = (size_t)A.rec_steps * base;
-    auto fetch = [&](int t) {
-        const size_t at = rbase + (size_t)t * SL;
+    for (int w = blockIdx.x; w < (A.count + 7) / 8 * 8 * NT; w += gridDim.x) {
+        const int q = w / 8 / NT * 8 + w % 8, s0 = w / 8 % NT * TS;
+        if (q >= A.count) continue;
+        const int base = A.robots[A.list[q]].slot_base;
+        const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+        // Absent nodes rest at their places with no adjoint and ghosts lie far off:
+        // both are written once, and their steps' values go to the entry past the
+        // tile's, so that every thread has the same loads in flight.
+        int to[NE], from[NE];
+        bool pres = false;
 #pragma unroll
         for (int e = 0; e < NE; ++e) {
-            xn[e] = *(const f32x4 *)&A.rec_x[at + from[e]];
-            ln[e] = *(const f32x4 *)&A.rec_l[at + from[e]];
-            if constexpr (DASH) vn[e] = *(const f32x4 *)&A.rec_u[at + from[e]];
-        }
-    };
-    auto stage = [&](int t) {
+            const int i = tid + e * TS, s = s0 + i;
+            const bool in = i < TL && s < SL;
+            float4 P0 = make_float4(1e4f, 1e4f, 1e4f, 0.f);
+            if (in) P0 = A.x0[base + s];
+            to[e] = P0.w != 0.f ? i : TL;
+            from[e] = in ? s : s0;
+            if (e == 0) pres = P0.w != 0.f;
+            P0.w = 0.f;
+            if (i < TL)
 #pragma unroll
-        for (int e = 0; e < NE; ++e) {
-            *(f32x4 *)&xs[t & 1][to[e]] = xn[e];
-            *(f32x4 *)&lf[t & 1][to[e]] = ln[e];
-            if constexpr (DASH) *(f32x4 *)&vs[t & 1][to[e]] = vn[e];
-        }
-    };
-    fetch(T - 1);
-    stage(T - 1);
-    fetch(T > 1 ? T - 2 : 0);
-    __syncthreads();
-    for (int t = T - 1; t >= 0; --t) {
-        const float2 sct = A.sc[t];
-        if (pres) {
-            const float4 *xb = xs[t & 1] + tid, *lb = lf[t & 1] + tid, *vb = vs[DASH ? t & 1 : 0] + (DASH ? tid : 0);
-            const float3 X = ld3(xb), L = ld3(lb), V = DASH ? ld3(vb) : X;
-            // the reads of direction d + 1 are issued before direction d's arithmetic
-            float3 Y = ld3(xb + dir_off(0, N)), LJ = ld3(lb + dir_off(0, N)), VJ = V;
-            if constexpr (DASH) VJ = ld3(vb + dir_off(0, N));
-#pragma unroll
-            for (int d = 0; d < NDIR; ++d) {
-                const float3 Yd = Y, Ld = LJ, Vd = VJ;
-                if (d + 1 < NDIR) {
-                    Y = ld3(xb + dir_off(d + 1, N));
-                    LJ = ld3(lb + dir_off(d + 1, N));
-                    if constexpr (DASH) VJ = ld3(vb + dir_off(d + 1, N));
+                for (int h = 0; h < 2; ++h) {
+                    xs[h][i] = P0;
+                    lf[h][i] = zero;
+                    if constexpr (DASH) vs[h][i] = zero;
                 }
-                float none = 0.f;
-                grad_spring<PHASE, DASH>(X, L, V, Yd, Ld, Vd, L0d(c, d), pk[d], pa[d], pb[d], pik[d], sct, gk[d],
-                                         gs[d], gc[d], DASH ? gd[DASH ? d : 0] : none);
-                __builtin_amdgcn_sched_barrier(0);
-            }
         }
-        if (t > 0) {
-            stage(t - 1);
-            fetch(t > 1 ? t - 2 : 0);
-        }
-        __syncthreads();
-    }
-    if (!pres) return;
+        if (!__syncthreads_or(pres)) continue;
+        const int pbase = NDIR * base + s0 + tid;
+        float pk[NDIR], pa[NDIR], pb[NDIR], pik[NDIR], gk[NDIR], gs[NDIR], gc[NDIR], gd[DASH ? NDIR : 1];
 #pragma unroll
-    for (int d = 0; d < NDIR; ++d) {
-        const int pi = pbase + d * SL;
-        A.gk[pi] = gk[d];
-        A.gs[pi] = gs[d];
-        A.gc[pi] = gc[d];
-        if constexpr (DASH) A.gd[pi] = gd[d];
+        for (int d = 0; d < NDIR; ++d) {
+            const int pi = pbase + d * SL;
+            pk[d] = pres ? A.pl.k[pi] : 0.f;
+            pa[d] = pres ? A.pl.kal[pi] : 0.f;
+            pb[d] = pres && PHASE ? A.pl.kbe[pi] : 0.f;
+            pik[d] = pk[d] != 0.f ? 1.0f / pk[d] : 0.f;
+            gk[d] = pres ? A.gk[pi] : 0.f;
+            gs[d] = pres ? A.gs[pi] : 0.f;
+            gc[d] = pres ? A.gc[pi] : 0.f;
+            if constexpr (DASH) gd[d] = pres ? A.gd[pi] : 0.f;
+        }
+        f32x4 xn[NE], ln[NE], vn[DASH ? NE : 1];
+        const size_t rbase = (size_t)A.rec_steps * base;
+        auto fetch = [&](int t) {
+            const size_t at = rbase + (size_t)t * SL;
+#pragma unroll
+            for (int e = 0; e < NE; ++e) {
+                xn[e] = *(const f32x4 *)&A.rec_x[at + from[e]];
+                ln[e] = *(const f32x4 *)&A.rec_l[at + from[e]];
+                if constexpr (DASH) vn[e] = *(const f32x4 *)&A.rec_u[at + from[e]];
+            }
+        };
+        auto stage = [&](int t) {
+#pragma unroll
+            for (int e = 0; e < NE; ++e) {
+                *(f32x4 *)&xs[t & 1][to[e]] = xn[e];
+                *(f32x4 *)&lf[t & 1][to[e]] = ln[e];
+                if constexpr (DASH) *(f32x4 *)&vs[t & 1][to[e]] = vn[e];
+            }
+        };
+        fetch(T - 1);
+        stage(T - 1);
+        fetch(T > 1 ? T - 2 : 0);
+        __syncthreads();
+        for (int t = T - 1; t >= 0; --t) {
+            const float2 sct = A.sc[t];
+            if (pres) {
+                const float4 *xb = xs[t & 1] + tid, *lb = lf[t & 1] + tid, *vb = vs[DASH ? t & 1 : 0] + (DASH ? tid : 0);
+                const float3 X = ld3(xb), L = ld3(lb), V = DASH ? ld3(vb) : X;
+                // the reads of direction d + 1 are issued before direction d's arithmetic
+                float3 Y = ld3(xb + dir_off(0, N)), LJ = ld3(lb + dir_off(0, N)), VJ = V;
+                if constexpr (DASH) VJ = ld3(vb + dir_off(0, N));
+#pragma unroll
+                for (int d = 0; d < NDIR; ++d) {
+                    const float3 Yd = Y, Ld = LJ, Vd = VJ;
+                    if (d + 1 < NDIR) {
+                        Y = ld3(xb + dir_off(d + 1, N));
+                        LJ = ld3(lb + dir_off(d + 1, N));
+                        if constexpr (DASH) VJ = ld3(vb + dir_off(d + 1, N));
+                    }
+                    float none = 0.f;
+                    grad_spring<PHASE, DASH>(X, L, V, Yd, Ld, Vd, L0d(c, d), pk[d], pa[d], pb[d], pik[d], sct, gk[d],
+                                             gs[d], gc[d], DASH ? gd[DASH ? d : 0] : none);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            if (t > 0) {
+                stage(t - 1);
+                fetch(t > 1 ? t - 2 : 0);
+            }
+            __syncthreads();
+        }
+        if (!pres) continue;
+#pragma unroll
+        for (int d = 0; d < NDIR; ++d) {
+            const int pi = pbase + d * SL;
+            A.gk[pi] = gk[d];
+            A.gs[pi] = gs[d];
+            A.gc[pi] = gc[d];
+            if constexpr (DASH) A.gd[pi] = gd[d];
+        }
     }
 }
 
@@ -1214,6 +1217,13 @@ struct AdjEntry {
     int gblock = 0;
     AdjFn g0 = nullptr, g0_phase = nullptr;
     int gy = 1;
+    // Tiles beside a reversal of few robots: up to this many rounds of tiles by
+    // 128 workgroups end before the reversal does, and the other half of the CUs
+    // is there when its next launch comes.  1200 steps backward, all tiles at
+    // once / 128 workgroups: 12^3, 64 robots 16.7 / 15.0 ms, 128 (9 rounds) with
+    // dashpots 45.4 / 39.0, 192 57.6 / 69.0; 11^3 with dashpots, 64 (4 rounds)
+    // 20.7 / 19.2, 96 (6) 24.1 / 27.3.
+    int rounds = 0;
 };
 #define SR_AE(NN, BS, X) \
     { NN, BS, k_adjoint<NN + 1, BS, false, X>, k_adjoint<NN + 1, BS, true, X> }
@@ -1234,8 +1244,8 @@ struct AdjEntry {
 #define SR_AESC_(NN, BS, LG, XC, GP)                                                                           \
     NN, BS, k_adjoint<NN + 1, BS, false, true, LG, false, false, false, true, XC, GP>,                          \
         k_adjoint<NN + 1, BS, true, true, LG, false, false, false, true, XC, GP>, SR_GT(NN, false)
-#define SR_AESC(NN, BS, LG, XC, GP) \
-    { SR_AESC_(NN, BS, LG, XC, GP) }
+#define SR_AESC(NN, BS, LG, XC, GP, ROUNDS) \
+    { SR_AESC_(NN, BS, LG, XC, GP), 0, nullptr, nullptr, 1, ROUNDS }
 #define SR_AESCG(NN, BS, LG, XC, GP, GBS, GY)                                                                  \
     {                                                                                                          \
         SR_AESC_(NN, BS, LG, XC, GP), GBS, k_adj_grad<NN + 1, GBS, false, GY>,                                  \
@@ -1244,7 +1254,7 @@ struct AdjEntry {
 const AdjEntry kAdj[] = {SR_AE(1, 64, true),    SR_AE(2, 64, true),    SR_AE(3, 64, true),   SR_AEL(4, 128, 2),
                          SR_AEL(5, 256, 2),     SR_AEL(6, 384, 2),     SR_AEL(7, 512, 2),    SR_AESL(8, 768, 2, 768),
                          SR_AESCG(9, 1024, 2, 2, false, 1024, 1), SR_AESCG(10, 768, 2, 3, false, 704, 2),
-                         SR_AESCG(11, 1024, 0, 4, false, 1024, 2), SR_AESC(12, 768, 0, 7, true)};
+                         SR_AESCG(11, 1024, 0, 4, false, 1024, 2), SR_AESC(12, 768, 0, 7, true, 9)};
 // spring dashpots or the damped ground (Table II model): the one-buffer
 // recompute form with the velocity terms
 #define SR_AED(NN, BS) \
@@ -1261,8 +1271,8 @@ const AdjEntry kAdj[] = {SR_AE(1, 64, true),    SR_AE(2, 64, true),    SR_AE(3, 
 #define SR_AEDS_(NN, BS, XC, GP, ...)                                                                          \
     NN, BS, k_adjoint<NN + 1, BS, false, true, 0, false, true, false, true, XC, GP>,                            \
         k_adjoint<NN + 1, BS, true, true, 0, false, true, false, true, XC, GP>, __VA_ARGS__
-#define SR_AEDS(NN, BS, XC, GP) \
-    { SR_AEDS_(NN, BS, XC, GP, SR_GT(NN, true)) }
+#define SR_AEDS(NN, BS, XC, GP, ROUNDS) \
+    { SR_AEDS_(NN, BS, XC, GP, SR_GT(NN, true)), 0, nullptr, nullptr, 1, ROUNDS }
 // last: SR_GT, or two nulls where the pass in GY workgroups is never slower
 #define SR_AEDSG(NN, BS, XC, GP, GBS, GY, ...)                                                                 \
     {                                                                                                          \
@@ -1273,8 +1283,8 @@ const AdjEntry kAdjD[] = {SR_AED(1, 64),        SR_AED(2, 64),        SR_AED(3, 
                           SR_AEDX(5, 256, 1),   SR_AEDX(6, 384, 1),   SR_AEDX(7, 512, 1),
                           SR_AEDSG(8, 768, 2, false, 768, 2, nullptr, nullptr),
                           SR_AEDSG(9, 1024, 3, false, 1024, 2, SR_GT(9, true)),
-                          SR_AEDSG(10, 768, 5, true, 768, 2, SR_GT(10, true)), SR_AEDS(11, 1024, 7, true),
-                          SR_AEDS(12, 768, 13, true)};
+                          SR_AEDSG(10, 768, 5, true, 768, 2, SR_GT(10, true)), SR_AEDS(11, 1024, 7, true, 5),
+                          SR_AEDS(12, 768, 13, true, 9)};
 
 }  // namespace
 
@@ -1322,7 +1332,7 @@ hipError_t launch_adjoint(int n, bool phase, const RobotInfo *robots, const int3
 hipError_t launch_adj_grad(int n, bool phase, const RobotInfo *robots, const int32_t *list, int count, Planes pl,
                            const float4 *x0, const float4 *rec_x, const float4 *rec_u, float4 *rec_l, int n_steps,
                            int rec_steps, const float2 *sc, float *gk, float *gs, float *gc, float *gd, SimConst c,
-                           bool beside, hipStream_t st) {
+                           bool beside, bool room, hipStream_t st) {
     const bool vel = c.dash || c.gdamp;
     if (vel && (!rec_u || !gd)) return hipErrorInvalidValue;
     const AdjEntry *e = nullptr;
@@ -1350,7 +1360,10 @@ hipError_t launch_adj_grad(int n, bool phase, const RobotInfo *robots, const int
         hipLaunchKernelGGL(phase ? e->g0_phase : e->g0, dim3(count, e->gy), dim3(e->gblock), 0, st, A);
     } else {
         const int slots = (n + 1) * (n + 1) * (n + 1), tiles = (slots + GRAD_TILE - 1) / GRAD_TILE;
-        hipLaunchKernelGGL(phase ? e->gt_phase : e->gt, dim3((count + 7) / 8 * 8 * tiles), dim3(GRAD_TILE), 0, st, A);
+        const int all = (count + 7) / 8 * 8 * tiles;
+        const bool half = beside && room && (all + 127) / 128 <= e->rounds;
+        const int grid = half && all > 128 ? 128 : all;
+        hipLaunchKernelGGL(phase ? e->gt_phase : e->gt, dim3(grid), dim3(GRAD_TILE), 0, st, A);
     }
     return hipGetLastError();
 }

@@ -132,12 +132,12 @@ hipError_t launch_record(int n, bool phase, bool vox, const RobotInfo *robots, c
 // reverse step over one recorded segment; for a side whose adjoint is split
 // (adjoint_is_split), rec_l (a buffer like rec_x) takes lambda_F of every step
 // and launch_adj_grad then forms the segment's parameter-gradient sums (beside: while
-// the next segment is reversed)
+// the next segment is reversed; room: with at most one other group on the GPU)
 bool adjoint_is_split(int n, bool vel);
 hipError_t launch_adj_grad(int n, bool phase, const RobotInfo *robots, const int32_t *list, int count, Planes pl,
                            const float4 *x0, const float4 *rec_x, const float4 *rec_u, float4 *rec_l, int n_steps,
                            int rec_steps, const float2 *sc, float *gk, float *gs, float *gc, float *gd, SimConst c,
-                           bool beside, hipStream_t st);
+                           bool beside, bool room, hipStream_t st);
 hipError_t launch_adjoint(int n, bool phase, const RobotInfo *robots, const int32_t *list, int count, Planes pl,
                           const float4 *x0, const float4 *rec_x, const float4 *rec_v, const float4 *rec_u,
                           float4 *rec_l, int n_steps, int rec_steps, const float2 *sc, float4 *lx, float4 *lv,

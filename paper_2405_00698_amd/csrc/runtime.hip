@@ -1125,7 +1125,7 @@ int pop_backward(sr_pop *pop, const float *dJ_dfitness, float *g_k, float *g_a, 
             HIPC(pop, launch_adj_grad(gr.n, pop->phase, pop->d_robots, pop->d_lists + gr.offset, gr.count, pop->pl,
                                       pop->x0, pop->rec_x[b], pop->rec_u[b], pop->rec_l[b], steps(seg), K,
                                       pop->adj_sc + (int64_t)seg * K, pop->gk, pop->gs, pop->gc, pop->gd, pop->c,
-                                      seg > 0, st));
+                                      seg > 0, ahead, st));
             HIPC(pop, hipEventRecord(event(SUMMED, g, b), st));
         }
         return SR_OK;
