@@ -143,7 +143,7 @@ __device__ int tournament(const GAArgs &A, const uint64_t *words) {
     return win;
 }
 
-__global__ __launch_bounds__(GB) void k_ga(GAArgs A, int chunk, int nch, int64_t first) {
+__global__ __launch_bounds__(GB) void k_ga_children(GAArgs A, int chunk, int nch, int64_t first) {
     const int64_t kids = (int64_t)(A.P - A.E) * nch, wg = first + blockIdx.x;
     if (wg >= kids) {
         ga_elite(A, (int)(wg - kids));
@@ -237,7 +237,7 @@ hipError_t launch_ga(const float *fit, const float *gin, float *gout, int P, int
     const int64_t total = (int64_t)(P - E) * nch + P, per = 1 << 23;  // a grid holds less than 2^32 threads
     for (int64_t first = 0; first < total; first += per) {
         const unsigned grid = (unsigned)(total - first < per ? total - first : per);
-        hipLaunchKernelGGL(k_ga, dim3(grid), dim3(GB), 0, st, A, chunk, nch, first);
+        hipLaunchKernelGGL(k_ga_children, dim3(grid), dim3(GB), 0, st, A, chunk, nch, first);
     }
     return hipGetLastError();
 }
