@@ -423,6 +423,13 @@ __device__ __forceinline__ float4 vox4(float4 v) { return v; }
 __device__ __forceinline__ void vox_store(float2 &d, float4 v) { d = make_float2(v.x, v.y); }
 __device__ __forceinline__ void vox_store(float4 &d, float4 v) { d = v; }
 
+// The pipelined 5^3 kernel is scheduled for four waves a SIMD (93 registers):
+// left to itself the compiler aims at six (79) and orders the reads so that a
+// step takes longer: 2000 steps of 256 / 1024 robots 2.41 / 4.30 -> 2.31 / 4.15
+// ms, and 1024 robots of 4^3 to 12^3, where its smaller waves also crowded the
+// other sides' CUs, 4000 steps 33.9 -> 31.7 ms.
+constexpr bool few_waves(int N, bool pipelined) { return N == 6 && pipelined; }
+
 // Template parameters of the persistent step kernel:
 //   N      lattice points per side (grid side + 1), so stencil offsets are immediates
 //   BS     threads per workgroup; each thread owns ceil(N^3 / BS) lattice slots
@@ -457,7 +464,9 @@ __device__ __forceinline__ void vox_store(float4 &d, float4 v) { d = v; }
 template <int N, int BS, int VAR, bool FENCE, bool PHASE, bool REC = false, bool WIDE = true, bool DASH = false,
           int VOX = 0, bool SBX = false, int LAG = 0, int LAGB = -1, bool BSWP = false, bool FSWP = false,
           int ROLL = 0, bool CLS = false, bool TCR = false, int PK = 1>
-__global__ __launch_bounds__(BS) void k_persist(PArgs A) {
+__global__ __launch_bounds__(BS)
+    __attribute__((amdgpu_waves_per_eu(1, few_waves(N, BSWP && PK == 1 && !(PHASE || REC || DASH)) ? 4 : 8))) void
+    k_persist(PArgs A) {
     constexpr int BR = BS / PK;  // threads per robot
     static_assert(BS % PK == 0 && BR % 64 == 0, "whole waves per robot");
     static_assert(PK == 1 || (!CLS && !REC && ROLL == 0), "packed robots use the plain slot mapping");
