@@ -167,11 +167,18 @@ int fail_hip(sr_pop *pop, hipError_t e, const char *what) {
         if ((pop)->sticky) return set_err((pop)->sticky, "population is in an error state"); \
     } while (0)
 
+// A refused allocation is reported by the call that made it and leaves nothing
+// for the next kernel launch to report as its own (hipGetLastError).
 template <class T>
 hipError_t dalloc(T **p, size_t count) {
     *p = nullptr;
     if (count == 0) count = 1;
-    return hipMalloc(reinterpret_cast<void **>(p), sizeof(T) * count);
+    const hipError_t e = hipMalloc(reinterpret_cast<void **>(p), sizeof(T) * count);
+    if (e != hipSuccess) {
+        *p = nullptr;
+        (void)hipGetLastError();
+    }
+    return e;
 }
 
 void clear_graphs(sr_pop *pop) {

@@ -1,0 +1,80 @@
+"""Host bookkeeping of a population where a device allocation is refused, with
+the HIP runtime replaced by a stand-in that counts allocations (hip_stub.cpp):
+the library's own code runs, no kernel does and no GPU is needed."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+LIBRARY = os.path.join(os.path.dirname(HERE), "paper_2405_00698_amd", "_lib.py")
+
+PRELUDE = """
+import ctypes as C, importlib.util, os, sys
+stub = C.CDLL(sys.argv[1], mode=os.RTLD_GLOBAL | os.RTLD_NOW)
+spec = importlib.util.spec_from_file_location("lib", sys.argv[2])
+lib = importlib.util.module_from_spec(spec)
+spec.loader.exec_module(lib)
+L = lib.load()
+some = C.c_void_p(64)  # stands for a caller's device array; nothing reads it
+
+def population(sides, params=None):
+    h = C.c_void_p()
+    p = params or lib.default_params()
+    assert L.pop_create(C.byref(p), len(sides), (C.c_int32 * len(sides))(*sides), None, C.byref(h)) == 0
+    return h
+
+def built(sides, params=None):
+    h = population(sides, params)
+    assert L.pop_build_from_voxels(h, some, some) == 0
+    return h
+
+def recorded(h, every, steps):
+    return L.pop_reset(h) or L.pop_record(h, every, steps) or L.pop_step(h, steps)
+
+def backward(h):
+    return L.pop_backward(h, some, some, some, some, None, None, None)
+
+def destroyed(h):
+    assert L.pop_destroy(h) == 0
+    assert stub.stub_bad_frees() == 0, "freed twice: %d" % stub.stub_bad_frees()
+    assert stub.stub_live() == 0, "left allocated: %d" % stub.stub_live()
+"""
+
+
+@pytest.fixture(scope="module")
+def stub(tmp_path_factory):
+    so = tmp_path_factory.mktemp("stub") / "hip_stub.so"
+    subprocess.check_call(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", os.path.join(HERE, "hip_stub.cpp"), "-o",
+                           str(so)])
+    return str(so)
+
+
+def run(stub, body):
+    r = subprocess.run([sys.executable, "-c", PRELUDE + body, stub, LIBRARY], capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+def test_refused_population_does_not_fail_the_next(stub):
+    """pop_create is refused at any one of its allocations, and so are the
+    checkpoints of pop_record: the next calls work."""
+    run(stub, '''
+stub.stub_fail(-1, -1)
+destroyed(built([5, 8, 12]))
+total = stub.stub_mallocs()
+assert total >= 20
+for n in range(total):
+    h, p = C.c_void_p(), lib.default_params()
+    stub.stub_fail(n, n + 1)
+    assert L.pop_create(C.byref(p), 3, (C.c_int32 * 3)(5, 8, 12), None, C.byref(h)) == lib.SR_ENOMEM, n
+    stub.stub_fail(-1, -1)
+    assert stub.stub_live() == 0, n
+    destroyed(built([5, 8, 12]))
+for n in range(2):
+    h = built([5, 8, 12])
+    stub.stub_fail(n, n + 1)
+    assert L.pop_record(h, 10, 40) == lib.SR_ENOMEM
+    assert recorded(h, 10, 40) == 0, (n, L.sr_last_error())
+    destroyed(h)
+''')
