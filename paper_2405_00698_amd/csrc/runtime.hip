@@ -1010,16 +1010,18 @@ namespace {
 int ensure_adj_scratch(sr_pop *pop, int K) {
     if (K <= pop->rec_cap) return SR_OK;
     HIPC(pop, hipStreamSynchronize(pop->st));
-    void *old[] = {pop->lx, pop->lv, pop->gk, pop->gs, pop->gc, pop->gd, pop->dJdw};
-    for (void *p : old)
-        if (p) HIPC(pop, hipFree(p));
-    for (int b = 0; b < NSET; ++b) {
-        void *seg[] = {pop->rec_x[b], pop->rec_v[b], pop->rec_u[b], pop->rec_l[b]};
-        for (void *p : seg)
-            if (p) HIPC(pop, hipFree(p));
-        pop->rec_u[b] = pop->rec_l[b] = nullptr;
-    }
-    pop->gd = nullptr;
+    // every pointer is null between its free and its allocation: if one is
+    // refused, the next call or pop_destroy must not free the others again
+    pop->rec_cap = 0;
+    auto drop = [](auto *&p) {
+        const hipError_t e = p ? hipFree(p) : hipSuccess;
+        p = nullptr;
+        return e;
+    };
+    for (float4 **p : {&pop->lx, &pop->lv}) HIPC(pop, drop(*p));
+    for (float **p : {&pop->gk, &pop->gs, &pop->gc, &pop->gd, &pop->dJdw}) HIPC(pop, drop(*p));
+    for (int b = 0; b < NSET; ++b)
+        for (float4 **p : {&pop->rec_x[b], &pop->rec_v[b], &pop->rec_u[b], &pop->rec_l[b]}) HIPC(pop, drop(*p));
     const size_t S = pop->total_slots;
     const bool vel = pop->c.dash || pop->c.gdamp;  // the reverse step needs v_n
     bool split = false;  // some side's reverse step hands lambda_F to a gradient pass
@@ -1043,10 +1045,7 @@ int ensure_adj_scratch(sr_pop *pop, int K) {
         e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
         if (e == hipSuccess) pop->adj_ev.push_back(ev);
     }
-    if (e != hipSuccess) {
-        pop->rec_cap = 0;
-        return set_err(SR_ENOMEM, "adjoint scratch: %s", hipGetErrorString(e));
-    }
+    if (e != hipSuccess) return set_err(SR_ENOMEM, "adjoint scratch: %s", hipGetErrorString(e));
     pop->rec_cap = K;
     return SR_OK;
 }

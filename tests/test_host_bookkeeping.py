@@ -78,3 +78,34 @@ for n in range(2):
     assert recorded(h, 10, 40) == 0, (n, L.sr_last_error())
     destroyed(h)
 ''')
+
+
+@pytest.mark.parametrize("sides", [[5, 5], [8, 12], [4, 6, 9]])
+@pytest.mark.parametrize("model", ["default", "table2"])
+def test_refused_adjoint_scratch(stub, sides, model):
+    """Growing the reverse sweep's scratch is refused at any one of its
+    allocations: the call reports it, and the population goes on, with a smaller
+    interval, the larger one once there is memory, or its end."""
+    run(stub, "sides, model = %r, %r\n" % (sides, model) + '''
+params = lib.table2_params() if model == "table2" else None
+h = built(sides, params)
+assert recorded(h, 10, 40) == 0
+stub.stub_fail(-1, -1)
+assert backward(h) == 0
+total = stub.stub_mallocs()  # the scratch and the time table
+assert total >= 13
+destroyed(h)
+for after in ("smaller", "same", "destroy"):
+    for n in range(total - 1):
+        h = built(sides, params)
+        assert recorded(h, 10, 40) == 0 and backward(h) == 0
+        assert recorded(h, 20, 40) == 0
+        stub.stub_fail(n, n + 1)
+        assert backward(h) == lib.SR_ENOMEM, n
+        stub.stub_fail(-1, -1)
+        if after == "smaller":
+            assert recorded(h, 5, 40) == 0 and backward(h) == 0, (n, L.sr_last_error())
+        elif after == "same":
+            assert backward(h) == 0, (n, L.sr_last_error())
+        destroyed(h)
+''')
