@@ -109,3 +109,17 @@ for after in ("smaller", "same", "destroy"):
             assert backward(h) == 0, (n, L.sr_last_error())
         destroyed(h)
 ''')
+
+
+@pytest.mark.parametrize("build", ["pop_build_from_voxels(h, some, some)", "pop_build_from_genomes(h, some, some, 0)"])
+def test_refused_counts_buffer(stub, build):
+    """The first build is refused its host buffer: it says so, and a later one works."""
+    run(stub, "build = lambda h: L.%s\n" % build + '''
+h = population([5, 8])
+stub.stub_fail_pinned(1)
+assert build(h) == lib.SR_ENOMEM
+assert L.pop_step(h, 1) == lib.SR_ESTATE
+stub.stub_fail_pinned(0)
+assert build(h) == 0 and L.pop_step(h, 1) == 0, L.sr_last_error()
+destroyed(h)
+''')
