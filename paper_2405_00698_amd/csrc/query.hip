@@ -99,10 +99,10 @@ __global__ __launch_bounds__(QB) __attribute__((amdgpu_waves_per_eu(4, 4))) void
     __shared__ float4 Ws[NFRAG];  // [layer][m][c][lane], then [c][lane] of the output layer
     __shared__ float bias[64 + 64 + 16];
     __shared__ float Bs[3 * SR_PE_M];
-    const int r = blockIdx.y;
+    const int r = blockIdx.x, part = blockIdx.y;
     const RobotInfo ri = robots[r];
     const int n = ri.n, nv = n * n * n;
-    if ((int)(blockIdx.x * tiles * 16) >= nv) return;
+    if (part * tiles * 16 >= nv) return;
     const float *g = genomes + (size_t)r * SR_GENOME_LEN;
     const int tid = threadIdx.x, lane = tid & 63;
     const int col = lane & 15, kq = lane >> 4;  // voxel column and k of this lane
@@ -129,8 +129,8 @@ __global__ __launch_bounds__(QB) __attribute__((amdgpu_waves_per_eu(4, 4))) void
     __syncthreads();
 
     const float inv = 1.0f / (float)n;
-    const int vend = min(nv, (int)(blockIdx.x + 1) * tiles * 16);
-    const int first = (blockIdx.x * tiles + (tid >> 6)) * 16;
+    const int vend = min(nv, (part + 1) * tiles * 16);
+    const int first = (part * tiles + (tid >> 6)) * 16;
     float4 next[TAB ? 4 : 1];  // the next tile's encoding
     auto fetch = [&](int v0) {
         const int v = v0 + col < nv ? v0 + col : nv - 1;
@@ -254,10 +254,10 @@ __global__ __launch_bounds__(QB) __attribute__((amdgpu_waves_per_eu(4, 8))) void
     __shared__ uint4 Ws[BNFRAG];  // [layer][m][K-block][lane], then [K-block][lane] of the output layer
     __shared__ float bias[64 + 64 + 6];
     __shared__ float Bs[3 * SR_PE_M];
-    const int r = blockIdx.y;
+    const int r = blockIdx.x, part = blockIdx.y;
     const RobotInfo ri = robots[r];
     const int n = ri.n, nv = n * n * n;
-    if ((int)(blockIdx.x * tiles * 16) >= nv) return;
+    if (part * tiles * 16 >= nv) return;
     const float *g = genomes + (size_t)r * SR_GENOME_LEN;
     const int tid = threadIdx.x, lane = tid & 63;
     const int col = lane & 15, kq = lane >> 4;  // voxel column and k quarter of this lane
@@ -284,8 +284,8 @@ __global__ __launch_bounds__(QB) __attribute__((amdgpu_waves_per_eu(4, 8))) void
     __syncthreads();
 
     const float inv = 1.0f / (float)n;
-    const int vend = min(nv, (int)(blockIdx.x + 1) * tiles * 16);
-    const int first = (blockIdx.x * tiles + (tid >> 6)) * 16;
+    const int vend = min(nv, (part + 1) * tiles * 16);
+    const int first = (part * tiles + (tid >> 6)) * 16;
     uint4 next[TAB ? 2 : 1];  // the next tile's encoding
     auto fetch = [&](int v0) {
         const int v = v0 + col < nv ? v0 + col : nv - 1;
@@ -392,7 +392,8 @@ hipError_t launch_query(const RobotInfo *robots, int R, uint32_t sides, const fl
     const int maxt = (max_side * max_side * max_side + 15) / 16;
     const int64_t want = (int64_t)R * maxt / (512 * 8);
     const int tiles = (int64_t)R * ((maxt + 3) / 4) <= 256 ? 4 : 8 * (int)(want < 1 ? 1 : want > 16 ? 16 : want);
-    const dim3 grid((maxt + tiles - 1) / tiles, R);
+    // robots in the grid's x: y ends at 65535, and a population of small robots may be larger
+    const dim3 grid(R, (maxt + tiles - 1) / tiles);
     if (bf)
         hipLaunchKernelGGL((table ? k_query_bf16<true> : k_query_bf16<false>), grid, dim3(QB), 0, st, robots, genomes,
                            B, cls, w, tiles, tab, static_cast<const uint4 *>(table));

@@ -1,5 +1,6 @@
 // Stand-in for the HIP runtime calls of libsoftrobot.so, for host tests of its
-// bookkeeping: memory calls keep count, every other call succeeds and does
+// bookkeeping: memory calls keep count, launches are checked for the size of
+// their grid, every other call succeeds and does
 // nothing (no kernel runs).  Loaded with RTLD_GLOBAL before the library, so the
 // library's calls bind here.
 #include <cstdlib>
@@ -12,6 +13,7 @@ int bad_frees = 0;         // frees of an address that is not allocated
 int mallocs = 0, streams = 0;
 int fail_from = -1, fail_to = -1;  // device allocations (numbered from 0) that fail
 bool fail_pinned = false;
+int bad_grids = 0;         // launches beyond what a grid holds
 int last = 0;              // what hipGetLastError returns next
 constexpr int kInvalid = 1, kOutOfMemory = 2;
 
@@ -32,6 +34,7 @@ extern "C" {
 void stub_fail(int from, int to) { mallocs = 0, fail_from = from, fail_to = to; }
 void stub_fail_pinned(int on) { fail_pinned = on; }
 int stub_bad_frees() { return bad_frees; }
+int stub_bad_grids() { return bad_grids; }
 int stub_live() { return (int)live.size(); }
 int stub_mallocs() { return mallocs; }
 int stub_streams() { return streams; }
@@ -84,7 +87,11 @@ struct Dim3 {
     unsigned x, y, z;
 };
 int hipLaunchKernel(const void *, Dim3, Dim3, void **, size_t, void *) { return 0; }
-int __hipPushCallConfiguration(Dim3, Dim3, size_t, void *) { return 0; }
+int __hipPushCallConfiguration(Dim3 g, Dim3 b, size_t, void *) {
+    // a grid holds less than 2^32 threads in x and at most 65535 workgroups in y and z
+    if (g.x == 0 || (unsigned long long)g.x * b.x >= 1ull << 32 || g.y > 65535 || g.z > 65535) ++bad_grids;
+    return 0;
+}
 int __hipPopCallConfiguration(Dim3 *g, Dim3 *b, size_t *m, void **s) {
     *g = *b = Dim3{1, 1, 1};
     return *m = 0, *s = nullptr, 0;

@@ -74,6 +74,24 @@ def test_query_split_does_not_change_bits(prec, copies):
     assert np.array_equal(many_w.view(np.uint32), np.tile(w, copies).view(np.uint32))
 
 
+@pytest.mark.parametrize("prec", [SR_QUERY_FP32, SR_QUERY_BF16])
+def test_query_of_more_robots_than_a_grid_row(prec):
+    """70,000 robots: more than a launch holds in any grid dimension but x.
+    Robot r has genome r mod 32, so every one is compared with one of few."""
+    from paper_2405_00698_amd.api import Population
+    few, R, side = 32, 70000, 2
+    B = inputs.gaussian_B()
+    G = inputs.random_genomes(few, seed=48)
+    _, cls, w = _gpu_query([side] * few, G, B, prec)
+    Gt = torch.from_numpy(G).to(DEV)[torch.arange(R, device=DEV) % few].contiguous()
+    P = Population([side] * R)
+    P.build_from_genomes(Gt, torch.from_numpy(B).to(DEV), prec)
+    many_cls, many_w = (q.cpu().numpy().reshape(R, -1) for q in P.query())
+    robot = np.arange(R) % few
+    assert np.array_equal(many_cls, cls.reshape(few, -1)[robot])
+    assert np.array_equal(many_w.view(np.uint32), w.reshape(few, -1)[robot].view(np.uint32))
+
+
 def test_bf16_and_fp32_builds_are_close():
     sides = [10] * 64
     B = inputs.gaussian_B()

@@ -39,6 +39,7 @@ def backward(h):
 def destroyed(h):
     assert L.pop_destroy(h) == 0
     assert stub.stub_bad_frees() == 0, "freed twice: %d" % stub.stub_bad_frees()
+    assert stub.stub_bad_grids() == 0, "launches beyond a grid's size: %d" % stub.stub_bad_grids()
     assert stub.stub_live() == 0, "left allocated: %d" % stub.stub_live()
 """
 
@@ -121,5 +122,15 @@ assert build(h) == lib.SR_ENOMEM
 assert L.pop_step(h, 1) == lib.SR_ESTATE
 stub.stub_fail_pinned(0)
 assert build(h) == 0 and L.pop_step(h, 1) == 0, L.sr_last_error()
+destroyed(h)
+''')
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_population_beyond_a_grid_row(stub, precision):
+    """70,000 robots: every launch of a generation stays within a grid."""
+    run(stub, "precision = %d\n" % precision + '''
+h = population([2] * 70000)
+assert L.pop_build_from_genomes(h, some, some, precision) == 0 and recorded(h, 10, 20) == 0 and backward(h) == 0
 destroyed(h)
 ''')
