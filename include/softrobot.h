@@ -187,8 +187,9 @@ int pop_set_graphs(sr_pop *pop, int32_t enable);
  *     through LDS: a population with zeta_spring != 0 accepts only those, any
  *     other population only the rest;
  *   +32 / +64 rebuild the diagonal / all springs' parameters each step from
- *     per-voxel terms (not after pop_set_spring_params); +128 keeps one
- *     position buffer;
+ *     per-voxel terms (not between pop_set_spring_params, which puts a
+ *     stored-parameter kernel in their place, and the next build, which takes
+ *     them up again); +128 keeps one position buffer;
  *   +256 * L keeps up to L + 1 neighbour reads in flight (L < 16);
  *   +4096 * (B + 1) sets the backward springs' reads apart (B in flight);
  *   +131072 / +262144 software-pipeline the backward / forward springs;

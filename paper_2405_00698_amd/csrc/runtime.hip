@@ -64,6 +64,9 @@ int noalloc_table(int dev, float2 **out) {
 struct SideGroup {
     int n, offset, count;
     PersistCfg cfg;
+    // the kernel that pop_set_spring_params replaced because it rebuilds the
+    // parameters from voxels (n 0: none); the next build takes it up again
+    PersistCfg from_vox{};
 };
 
 struct GraphKey {
@@ -261,6 +264,12 @@ int finish_build(sr_pop *pop) {
     pop->built = pop->h_built[0] < 0;
     if (!pop->built) return set_err(SR_EINVAL, "robot %d has a voxel class outside 0..4", (int)pop->h_built[0]);
     pop->vox_ok = true;
+    for (auto &g : pop->groups)
+        if (g.from_vox.n && persist_supported(g.from_vox, pop->phase)) {
+            g.cfg = g.from_vox;
+            g.from_vox = {};
+            clear_graphs(pop);
+        }
     return SR_OK;
 }
 
@@ -585,6 +594,7 @@ int pop_set_step_config(sr_pop *pop, int32_t mode, int32_t block, int32_t steps_
                 PersistCfg c{g.n, block, var + (pop->dash ? 16 : 0)};
                 if (persist_supported(c, pop->phase)) {
                     g.cfg = c;
+                    g.from_vox = {};
                     found = true;
                     break;
                 }
@@ -641,6 +651,7 @@ int pop_set_persist_variant(sr_pop *pop, int32_t n, int32_t block, int32_t varia
                 return set_err(SR_EUNSUPPORTED, "variant %d %s spring dashpots; this population has %s", variant,
                                (variant & 16) ? "has" : "lacks", pop->dash ? "them" : "none");
             g.cfg = c;
+            g.from_vox = {};
             clear_graphs(pop);
             return SR_OK;
         }
@@ -929,6 +940,7 @@ int pop_set_spring_params(sr_pop *pop, const float *k, const float *a, const flo
     pop->vox_ok = false;
     for (auto &g : pop->groups)
         if (g.cfg.variant & 96) {
+            g.from_vox = g.cfg;
             g.cfg.block = persist_default_block(g.n, pop->dash, false, pop->R <= kCUs, &g.cfg.variant);
             clear_graphs(pop);
         }

@@ -334,3 +334,25 @@ def test_phase_kernels_bitwise_equal_per_step_kernel(n):
         P.step(150)
         x, vv, _ = P.state()
         assert torch.equal(x, xr) and torch.equal(vv, vr), (b, v)
+
+
+@pytest.mark.parametrize("n", [5, 12])
+def test_rebuild_after_set_spring_params_equals_a_fresh_population(n):
+    """Parameters with phases set on a population without any, then another
+    build: kernel, springs and steps are those of a population that never had
+    its parameters set (at 12^3 the kernel that rebuilds them from voxels)."""
+    from paper_2405_00698_amd import api, default_params
+    sides = [n, 4]
+    cls, w = (torch.from_numpy(q).to(DEV) for q in voxel_population(sides, 71))
+    P, Q = (api.Population(sides, params=default_params(zeta_spring=0.1)) for _ in range(2))
+    P.build_from_voxels(cls, w)
+    P.set_spring_params(None, None, torch.linspace(0.1, 3.0, P.counts()[3][-1], device=DEV))
+    P.step(20)
+    for q in (P, Q):
+        q.build_from_voxels(cls, w)
+        q.step(60)
+    assert P.persist_variant(n) == Q.persist_variant(n)
+    for a, b in zip(P.springs().values(), Q.springs().values()):
+        assert torch.equal(a, b)
+    for a, b in zip(P.state()[:2], Q.state()[:2]):
+        assert torch.equal(a, b)

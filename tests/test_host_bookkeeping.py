@@ -134,3 +134,37 @@ h = population([2] * 70000)
 assert L.pop_build_from_genomes(h, some, some, precision) == 0 and recorded(h, 10, 20) == 0 and backward(h) == 0
 destroyed(h)
 ''')
+
+
+def test_rebuild_takes_up_the_voxel_kernel_again(stub):
+    """pop_set_spring_params replaces the kernels that rebuild the parameters
+    from voxels until the next build, unless another kernel was chosen since."""
+    run(stub, '''
+VOX = 96
+def variant(h, n):
+    b, v = C.c_int32(), C.c_int32()
+    assert L.pop_get_persist_variant(h, n, C.byref(b), C.byref(v)) == 0
+    return b.value, v.value
+def configs(n):
+    b, v = (C.c_int32 * 64)(), (C.c_int32 * 64)()
+    return [(b[i], v[i]) for i in range(L.sr_persist_configs(n, b, v, 64))]
+for params, n in ((lib.table2_params(), 12), (lib.default_params(), 11), (lib.default_params(), 5)):
+    dash = params.zeta_spring != 0
+    vox = [c for c in configs(n) if bool(c[1] & 16) == dash and c[1] & VOX]
+    plane = [c for c in configs(n) if bool(c[1] & 16) == dash and not c[1] & VOX]
+    for own in [None] + vox:
+        h = built([5, n, n], params)
+        if own:
+            assert L.pop_set_persist_variant(h, n, *own) == 0
+        before = variant(h, n)
+        assert L.pop_set_spring_params(h, some, some, some) == 0 and L.pop_step(h, 3) == 0
+        assert not variant(h, n)[1] & VOX
+        assert L.pop_build_from_voxels(h, some, some) == 0 and L.pop_step(h, 3) == 0
+        assert variant(h, n) == before, (n, own)
+        # a kernel chosen after the parameters stays
+        assert L.pop_set_spring_params(h, some, None, None) == 0
+        assert L.pop_set_persist_variant(h, n, *plane[-1]) == 0
+        assert L.pop_build_from_voxels(h, some, some) == 0
+        assert variant(h, n) == plane[-1]
+        destroyed(h)
+''')
