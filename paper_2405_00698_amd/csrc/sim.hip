@@ -423,6 +423,30 @@ __device__ __forceinline__ float4 vox4(float4 v) { return v; }
 __device__ __forceinline__ void vox_store(float2 &d, float4 v) { d = make_float2(v.x, v.y); }
 __device__ __forceinline__ void vox_store(float4 &d, float4 v) { d = v; }
 
+// Where a launch that starts at a checkpoint writes it.  The two stores between
+// the state's loads need no second read of it, but move the registers of the
+// step loop by a few, for better or worse; in a loop of their own at the head of
+// the kernel they do not touch it.  Us a step with the stores between the loads ->
+// at the head, 30 / 256 / 1024 robots: dashpots 6^3 1.62 / 1.77 / 6.45 -> 1.56 / 1.69 /
+// 6.36, 7^3 1.64 / 1.86 / 6.03 -> 1.61 / 1.83 / 5.95, 8^3 (136 -> 132 registers) 2.20 / 2.50 /
+// 9.63 -> 2.20 / 2.52 / 9.53, 9^3 2.75 / 3.27 / 12.2 -> 2.68 / 3.19 / 12.0; but 11^3 5.91 /
+// 8.26 / 32.0 -> 6.28 / 8.99 / 35.4, 10^3 3.31 / 3.84 / 14.4 -> 3.32 / 3.94 / 14.6, 4^3 1.40 /
+// 1.44 / 1.88 -> 1.42 / 1.46 / 1.83; without dashpots 1^3 1.50 / 1.46 / 1.88 -> 1.47 / 1.43 /
+// 1.86, others within 1.6 % either way or slower (9^3 1.98 / 2.28 / 8.78 -> 2.00 / 2.34 / 8.83).
+constexpr bool checkpoint_ahead(int N, bool dash) { return dash ? N >= 6 && N <= 10 : N == 2; }
+
+// the state of this workgroup's robots
+template <int SL, int BS>
+__device__ __forceinline__ void write_checkpoint(const PArgs &A) {
+    for (int q = blockIdx.x; q < A.count; q += gridDim.x) {
+        const int base = A.robots[A.list[q]].slot_base;
+        for (int s = threadIdx.x; s < SL; s += BS) {
+            A.ck_x[base + s] = A.x[base + s];
+            A.ck_v[base + s] = A.v[base + s];
+        }
+    }
+}
+
 // The pipelined 5^3 kernel is scheduled for four waves a SIMD (93 registers):
 // left to itself the compiler aims at six (79) and orders the reads so that a
 // step takes longer: 2000 steps of 256 / 1024 robots 2.41 / 4.30 -> 2.31 / 4.15
@@ -536,6 +560,8 @@ __global__ __launch_bounds__(BS)
         }
     }
 
+    static_assert(PK == 1 || !checkpoint_ahead(N, DASH), "one robot a workgroup in write_checkpoint");
+    if (!REC && checkpoint_ahead(N, DASH) && A.ck_x) write_checkpoint<SL, BS>(A);
     for (int q0 = blockIdx.x * PK; q0 < A.count; q0 += gridDim.x * PK) {
         // a packed workgroup steps all its robots together: one without a
         // robot (or with a diverged one) has no live slot but keeps the barriers
@@ -581,7 +607,7 @@ __global__ __launch_bounds__(BS)
             const float4 X = A.x[base + sc_];
             const float4 V = A.v[base + sc_];
             if (live) {
-                if (!REC && A.ck_x) {
+                if (!REC && !checkpoint_ahead(N, DASH) && A.ck_x) {
                     A.ck_x[base + s] = X;
                     A.ck_v[base + s] = V;
                 }

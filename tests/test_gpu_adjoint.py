@@ -385,3 +385,24 @@ def test_gradient_pass_forms_give_the_same_bits(n, dash):
         else:
             for a, b in zip(g, ref):
                 assert np.array_equal(a, b), K
+
+
+@pytest.mark.parametrize("n,dash", [(1, False), (5, True), (6, True), (7, True), (8, True), (9, True)])
+def test_checkpoints_written_ahead_of_the_steps(n, dash):
+    """Sides whose step kernel writes the checkpoint in a loop of its own: the
+    gradients do not depend on how many checkpoints there are."""
+    from paper_2405_00698_amd import table2_params
+    from paper_2405_00698_amd.api import Population
+    sides = [n] * 3
+    cls, w = voxel_population(sides, 72, p_empty=0.0 if n == 1 else 0.3)
+    ref = None
+    for K in (40, 7, 1):
+        P = Population(sides, params=table2_params() if dash else None)
+        P.build_from_voxels(torch.from_numpy(cls).to(DEV), torch.from_numpy(w).to(DEV))
+        P.record(K, 40)
+        P.step(40)
+        g = [q.cpu().numpy() for q in P.backward(torch.ones(3, device=DEV)).values()]
+        assert np.abs(g[0]).max() > 0
+        ref = ref or g
+        for a, b in zip(g, ref):
+            assert np.array_equal(a, b), K
