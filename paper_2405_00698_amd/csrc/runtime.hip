@@ -1020,8 +1020,10 @@ int pop_record(sr_pop *pop, int32_t checkpoint_every, int32_t max_steps) {
         }
         pop->ck_alloc = cap;
     }
-    // created one after another, so that the runtime deals them to different hardware queues
-    e = add_streams(pop->rec_st, REC_LANES);
+    // created one after another, so that the runtime deals them to different
+    // hardware queues; one group has its lane and those of pop_backward's
+    // recomputation and gradient passes (a stream takes about 80 us to make)
+    e = add_streams(pop->rec_st, pop->groups.size() == 1 ? 3 : REC_LANES);
     if (e != hipSuccess) return fail_hip(pop, e, "recording streams");
     pop->ck_every = checkpoint_every;
     pop->ck_cap = cap;

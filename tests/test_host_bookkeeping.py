@@ -168,3 +168,17 @@ for params, n in ((lib.table2_params(), 12), (lib.default_params(), 11), (lib.de
         assert variant(h, n) == plane[-1]
         destroyed(h)
 ''')
+
+
+@pytest.mark.parametrize("sides,lanes", [([8, 8], 3), ([5, 12], 4), ([4, 5, 6, 7, 8], 4)])
+def test_recording_makes_the_streams_it_uses(stub, sides, lanes):
+    """A stream costs the first recording of a population about 80 us."""
+    run(stub, "sides, lanes = %r, %d\n" % (sides, lanes) + '''
+h = built(sides)
+before = stub.stub_streams()
+assert L.pop_record(h, 10, 40) == 0
+assert stub.stub_streams() - before == lanes
+assert L.pop_step(h, 40) == 0 and backward(h) == 0 and recorded(h, 10, 40) == 0
+assert stub.stub_streams() - before == lanes
+destroyed(h)
+''')
