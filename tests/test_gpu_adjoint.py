@@ -406,3 +406,43 @@ def test_checkpoints_written_ahead_of_the_steps(n, dash):
         ref = ref or g
         for a, b in zip(g, ref):
             assert np.array_equal(a, b), K
+
+
+@pytest.mark.parametrize("dash", [False, True])
+@pytest.mark.parametrize("pair", [(8, 12), (5, 11), (4, 6), (9, 10)])
+def test_two_group_gradients_are_those_of_each_alone(pair, dash):
+    """Two sides share one recomputation stream, one stream of gradient passes and
+    the segment buffers.  Two split reverse steps, a fused and a split one, two
+    fused ones (with dashpots 9^3 and 10^3 sum beside the reversal in two parts,
+    12^3 and 11^3 in tiles); two segments more than buffer sets, the last one
+    short, and one step in a segment of its own."""
+    from paper_2405_00698_amd import table2_params
+    from paper_2405_00698_amd.api import Population
+    params = table2_params() if dash else None
+    sides = [pair[i % 3 == 0] for i in range(15)]  # ten of the first, five of the second
+    cls, w = voxel_population(sides, 73, p_empty=0.25)
+    at = np.concatenate([[0], np.cumsum([n ** 3 for n in sides])])
+
+    def gradients(robots, K, steps):
+        P = Population([sides[r] for r in robots], params=params)
+        P.build_from_voxels(torch.from_numpy(np.concatenate([cls[at[r]:at[r + 1]] for r in robots])).to(DEV),
+                            torch.from_numpy(np.concatenate([w[at[r]:at[r + 1]] for r in robots])).to(DEV))
+        dJ = torch.tensor([1.0 + 0.1 * r for r in robots], device=DEV)
+        out = []
+        for _ in range(2):  # the second on the buffers that the first has left
+            P.reset()
+            P.record(K, steps)
+            P.step(steps)
+            out.append([g.cpu().numpy() for g in P.backward(dJ).values()])
+        for a, b in zip(*out):
+            assert np.array_equal(a, b)
+        off = np.concatenate([[0], np.cumsum(P.counts()[1])])
+        return {r: [g[off[i]:off[i + 1]] for g in out[0]] for i, r in enumerate(robots)}
+
+    for K, steps in ((30, 30 * 4 + 17), (30, 30 * 3 + 1), (40, 25)):
+        together = gradients(list(range(len(sides))), K, steps)
+        for n in pair:
+            alone = gradients([r for r in range(len(sides)) if sides[r] == n], K, steps)
+            for r, g in alone.items():
+                for a, b in zip(g, together[r]):
+                    assert np.array_equal(a, b), (K, steps, n, r)

@@ -102,3 +102,23 @@ def test_poisoned_dashpot_kernels_give_the_same_bits():
     b = _run(poison, sides, cls, w, configs, 120, params=params)
     for cfg, ra, rb in zip(configs, a, b):
         assert np.isfinite(rb[0]).all() and all(np.array_equal(p, q) for p, q in zip(ra, rb)), cfg
+
+
+@pytest.mark.parametrize("n", [9, 11, 12])
+def test_poisoned_dashpot_kernels_of_the_largest_sides(n):
+    """Every dashpot step kernel of a side, among them (12^3) the one in chunks of
+    three directions with two alternating sets of rows, and the recording ones
+    and the reverse step (three chunks at 9^3, seven at 11^3, thirteen at 12^3,
+    the largest two with each chunk's parameters read from the planes)."""
+    poison = _lib.load(build_lib.LIB_POISON)
+    prod = _lib.load()
+    sides = [n] * 3
+    cls, w = voxel_population(sides, 160 + n, p_empty=0.3)
+    params = _lib.table2_params()
+    configs = [(n, b, v) for b, v in api.persist_configs(n) if v & 16]
+    a = _run(prod, sides, cls, w, configs, 120, params=params, record=True)
+    b = _run(poison, sides, cls, w, configs, 120, params=params, record=True)
+    for cfg, ra, rb in zip(configs, a, b):
+        assert all(np.isfinite(q).all() for q in rb), cfg
+        assert all(np.array_equal(p, q) for p, q in zip(ra, rb)), cfg
+    say("side", n, "dashpot configurations compared", len(configs))
