@@ -5,8 +5,8 @@ whole population, a few launch schedules of the size groups (which stream each
 side's launch goes to, in which order; several grid sides only) together with
 the number of steps per launch (the whole call, or the call split into shorter
 launches).  Results are cached in a JSON file keyed by
-(device name, side, population bucket, spring model, the library's
-configuration list for that side)."""
+(device name, side, population bucket, whether every robot has a CU, spring
+model, the library's configuration list for that side)."""
 import hashlib
 import json
 import os
@@ -15,6 +15,8 @@ import time
 import torch
 
 from . import api
+
+CUS = 256  # compute units of an MI355X
 
 
 def _bucket(count):
@@ -71,7 +73,11 @@ def tune(pop, steps=200, cache_path=None, verbose=False):
     for n, cnt in sorted(counts.items()):
         configs = api.persist_configs(n)
         lib = hashlib.sha256(repr(configs).encode()).hexdigest()[:12]
-        key = "%s|n=%d|R<=%d%s|%s" % (dev_name, n, _bucket(cnt), "|dash" if pop.dashpots else "", lib)
+        # the library's default depends on whether every robot of the population
+        # has a CU; one side's robots alone may have one where the whole do not
+        default = pop.persist_variant(n)
+        key = "%s|n=%d|R<=%d%s%s|%s" % (dev_name, n, _bucket(cnt), "|alone" if len(pop.sides) <= CUS else "",
+                                        "|dash" if pop.dashpots else "", lib)
         if key in cache:
             b, v, t = cache[key]
             try:
@@ -81,7 +87,6 @@ def tune(pop, steps=200, cache_path=None, verbose=False):
             except api.SoftRobotError:
                 pass  # not usable for this population (e.g. spring parameters set directly): time again
         target = pop if len(counts) == 1 else _sub_population(pop, n)
-        default = target.persist_variant(n)
         times = []
         for b, v in configs:
             if bool(v & 16) != pop.dashpots:
