@@ -182,3 +182,44 @@ def test_default_kernel_at_8_by_population(robots):
     n = a[0].shape[0]
     assert np.array_equal(a[0].cpu().numpy(), b[0][:n].cpu().numpy())
     assert np.array_equal(a[1].cpu().numpy(), b[1][:n].cpu().numpy())
+
+
+@pytest.mark.parametrize("sides", [[8, 8], [5, 12, 5], [4, 7, 9, 8, 12, 4]])
+def test_recorded_run_under_capture(sides):
+    """pop_reset and a recorded pop_step_noalloc of one, two and five side groups
+    in a caller's graph: every replay, with eager work between, leaves the state
+    and the checkpoints of the eager run."""
+    from paper_2405_00698_amd.api import Population
+    cls, w = (torch.from_numpy(q).to(DEV) for q in voxel_population(sides, 74))
+    dJ = torch.ones(len(sides), device=DEV)
+
+    def outputs(P):
+        return [q.cpu().numpy() for q in list(P.state()[:2]) + [P.fitness()] + list(P.backward(dJ).values())]
+
+    eager = Population(sides)
+    eager.build_from_voxels(cls, w)
+    eager.record(20, 70)
+    eager.step(70)
+    want = outputs(eager)
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st):
+        P = Population(sides, stream=st)
+        P.build_from_voxels(cls, w)
+        P.record(20, 70)
+        P.reset()
+        P.step_noalloc(70)
+        st.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=st):
+            P.reset()
+            P.step_noalloc(70)
+        for rep in range(3):
+            P.reset()
+            P.step_noalloc(30 + rep)  # eager, leaves other checkpoints and another state
+            st.synchronize()
+            P.reset()
+            P.step_noalloc(70)        # the host's step count as the graph leaves it
+            graph.replay()
+            for a, b in zip(outputs(P), want):
+                assert np.array_equal(a, b), rep
+        P.close()
