@@ -172,8 +172,10 @@ int sr_microbench(int32_t which, int32_t iters, double *seconds, double *units);
 int sr_persist_configs(int32_t n, int32_t *blocks, int32_t *variants, int32_t cap);
 
 /* Steps without checkpoints run as captured HIP graphs (one per step count,
- * step form and state buffer), with one parallel branch per grid side;
- * enable = 0 launches the kernels directly instead.  On by default. */
+ * step form and state buffer), with one parallel branch per grid side; a call
+ * that puts several launches on a lane beside other lanes (a schedule that
+ * shares lanes, several launches per call) launches them directly, and
+ * enable = 0 launches every kernel directly.  On by default. */
 int pop_set_graphs(sr_pop *pop, int32_t enable);
 
 /* Picks the persistent kernel for robots of side n: block threads per

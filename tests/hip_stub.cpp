@@ -10,7 +10,7 @@
 namespace {
 std::set<void *> live;     // device and pinned allocations
 int bad_frees = 0;         // frees of an address that is not allocated
-int mallocs = 0, streams = 0;
+int mallocs = 0, streams = 0, captures = 0;
 int fail_from = -1, fail_to = -1;  // device allocations (numbered from 0) that fail
 bool fail_pinned = false;
 int bad_grids = 0;         // launches beyond what a grid holds
@@ -38,6 +38,7 @@ int stub_bad_grids() { return bad_grids; }
 int stub_live() { return (int)live.size(); }
 int stub_mallocs() { return mallocs; }
 int stub_streams() { return streams; }
+int stub_captures() { return captures; }
 
 int hipMalloc(void **p, size_t) {
     const int n = mallocs++;
@@ -71,7 +72,7 @@ int hipStreamCreateWithFlags(void **s, unsigned) { return ++streams, *s = token(
 int hipStreamDestroy(void *) { return 0; }
 int hipStreamSynchronize(void *) { return 0; }
 int hipStreamWaitEvent(void *, void *, unsigned) { return 0; }
-int hipStreamBeginCapture(void *, int) { return 0; }
+int hipStreamBeginCapture(void *, int) { return ++captures, 0; }
 int hipStreamEndCapture(void *, void **g) { return *g = token(), 0; }
 int hipGraphInstantiate(void **e, void *, void *, char *, size_t) { return *e = token(), 0; }
 int hipGraphLaunch(void *, void *) { return 0; }

@@ -182,3 +182,39 @@ assert L.pop_step(h, 40) == 0 and backward(h) == 0 and recorded(h, 10, 40) == 0
 assert stub.stub_streams() - before == lanes
 destroyed(h)
 ''')
+
+
+def test_only_graphs_of_one_launch_a_lane_are_captured(stub):
+    """Several launches on a lane beside other lanes go out directly; a single
+    side, the per-step form and one launch a lane are captured once per length."""
+    run(stub, '''
+def captured(h, *lengths):
+    before = stub.stub_captures()
+    for n in lengths:
+        assert L.pop_step(h, n) == 0
+    return stub.stub_captures() - before
+def schedule(h, sides, lanes):
+    n = len(sides)
+    assert L.pop_set_schedule(h, n, (C.c_int32 * n)(*sides), (C.c_int32 * n)(*lanes)) == 0
+AUTO, PLAIN = 0, 2
+h = built([5, 8, 12, 5])
+assert captured(h, 100, 100, 30) == 2              # the default: a lane for each side
+assert L.pop_set_step_config(h, AUTO, 0, 50) == 0
+assert captured(h, 100, 51) == 0                   # several launches a call
+assert captured(h, 50, 20) == 2
+assert L.pop_set_step_config(h, AUTO, 0, 0) == 0
+schedule(h, [12, 8, 5], [0, 1, 0])
+assert captured(h, 100, 30) == 0                   # two sides on a lane
+schedule(h, [12, 8, 5], [2, 0, 1])
+assert captured(h, 100) == 1
+schedule(h, [12, 8, 5], [0, 0, 0])
+assert L.pop_set_step_config(h, PLAIN, 0, 0) == 0
+assert captured(h, 10) == 1
+destroyed(h)
+h = built([6, 6])
+assert L.pop_set_step_config(h, AUTO, 0, 25) == 0
+assert captured(h, 100) == 1                       # one lane: a chain
+assert L.pop_set_graphs(h, 0) == 0
+assert captured(h, 100) == 0
+destroyed(h)
+''')
