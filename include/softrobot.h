@@ -17,7 +17,10 @@
  *    pointers marked "host" are host memory.  The caller owns all of them; the
  *    library never frees or keeps them past the call.
  *  - Every device call is asynchronous on the stream given to pop_create (or
- *    to the free function); calls that return host data synchronise it.
+ *    to the free function), except that a build, which reports a bad class and
+ *    leaves the counts on the host, and pop_set_state synchronise it, and that
+ *    calls that enlarge a buffer (a longer step call, pop_record, pop_backward)
+ *    wait for it first.
  *  - Voxel arrays are concatenated over robots in robot order; robot r holds
  *    n_r^3 entries with linear id i + n_r (j + n_r k) (x fastest, z up).
  *  - Node (mass) ids of a robot are its lattice points (a, b, c) in [0, n]^3
@@ -288,9 +291,10 @@ int pop_backward(sr_pop *pop, const float *dJ_dfitness, float *g_k, float *g_a, 
  * and for a robot with no occupied voxel (it has no body). */
 int pop_fitness(sr_pop *pop, float *fitness);
 
-/* Introspection (host outputs; synchronise the stream).  Any pointer may be
- * NULL.  n_masses / n_springs: host [n_robots]; mass_offset / spring_offset:
- * host [n_robots + 1] prefix sums. */
+/* Introspection.  Any pointer may be NULL.  The counts (host outputs) are
+ * ready when the build returns: pop_get_counts does no device work and does not
+ * synchronise.  n_masses / n_springs: host [n_robots]; mass_offset /
+ * spring_offset: host [n_robots + 1] prefix sums. */
 int pop_get_counts(sr_pop *pop, int32_t *n_masses, int32_t *n_springs, int64_t *mass_offset,
                    int64_t *spring_offset);
 /* kept (dev uint8, concatenated n_r^3): class of kept voxels, 0 elsewhere;

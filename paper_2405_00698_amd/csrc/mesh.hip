@@ -82,7 +82,7 @@ __device__ __forceinline__ float4 term_load(float4 v) { return v; }
 // that need them); for a few robots the chain of barriers (component labels
 // take 5 to 15 rounds).  Each voxel's terms are formed once, not once for each
 // of its 28 springs.  Measured against one 1024-thread workgroup per robot that
-// wrote all of those: 4096 robots of 10^3 1350 -> 215 us (4.6 TB/s), 1024
+// wrote all of those: 4096 robots of 10^3 1350 -> 186 us (5.3 TB/s), 1024
 // uneven robots 348 -> 40 us, 30 of 5^3 41 -> 10 us.
 // BT 256 for grids up to 6^3 (216 voxels): larger workgroups only add waves to
 // every barrier there.

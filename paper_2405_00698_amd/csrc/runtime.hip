@@ -124,9 +124,7 @@ struct sr_pop {
     int ck_every = 0, ck_cap = 0, ck_alloc = 0;
     bool rec_valid = false;
     float4 *ck_x = nullptr, *ck_v = nullptr;
-    // adjoint scratch (grown on demand)
-    // (two sets of segment buffers: segment s - 1 is recomputed on adj_st while
-    // segment s is reversed on the population's stream)
+    // adjoint scratch (grown on demand), for checkpoint intervals up to rec_cap
     int rec_cap = 0;
     // three sets: while segment s is reversed, segment s - 1 is recomputed and
     // (split form) the gradient passes of segment s + 1 still read theirs
@@ -492,7 +490,9 @@ int pop_create(const sr_sim_params *params, int32_t n_robots, const int32_t *gri
     // Recorded runs and reverse sweeps: the groups dealt, longest first, to the
     // least loaded of REC_LANES streams.  A group's time is its turns on 256 CUs
     // times that of one robot on a CU, in us a step for recording and reversing
-    // (Table II model; sides up to 7^3 are latency bound and alike).  Four lanes
+    // (Table II model; sides up to 7^3 are latency bound and alike; without dashpots
+    // a reversal takes 0.52 to 0.64 of it at every side, 3.1, 3.5, 3.6, 3.9, 6.4, 7.7,
+    // 10.2, 13.0, 17.6 us from 4^3 to 12^3, so the groups are dealt alike).  Four lanes
     // are what the device's four hardware queues run at once; a stream beyond
     // them only waits behind another one.  From three groups on the last lane
     // also carries the gradient passes, counted in from the start.

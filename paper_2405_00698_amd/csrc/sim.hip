@@ -451,7 +451,10 @@ __device__ __forceinline__ void write_checkpoint(const PArgs &A) {
 // left to itself the compiler aims at six (79) and orders the reads so that a
 // step takes longer: 2000 steps of 256 / 1024 robots 2.41 / 4.30 -> 2.31 / 4.15
 // ms, and 1024 robots of 4^3 to 12^3, where its smaller waves also crowded the
-// other sides' CUs, 4000 steps 33.9 -> 31.7 ms.
+// other sides' CUs, 4000 steps 33.9 -> 31.7 ms.  Alone it takes as long with 123
+// registers (no checkpoint stores between the loads); beside other sides that
+// decides what it shares a CU with: 1000 robots of 4^3 to 6^3 2.72 us a step with 93
+// against 2.48, 300 of 5^3 to 8^3 2.78 against 2.40, but 1000 of them 3.95 against 4.85.
 constexpr bool few_waves(int N, bool pipelined) { return N == 6 && pipelined; }
 
 // Template parameters of the persistent step kernel:
@@ -1360,7 +1363,9 @@ __device__ __forceinline__ void spring_polar(float kL0, float kal, float kbe, fl
     }
 }
 
-// The springs in canonical order: 24 B each, at the rate of memory.
+// The springs in canonical order: 24 B each written, 12 B of planes read.  27 us
+// for the 1.65 M springs of 256 robots of 8^3: 2.2 TB/s, less than half the copy
+// rate; a chain of dependent loads (slot, robot, offset, plane) in a short launch.
 __global__ __launch_bounds__(EACH_THREADS) void k_springs_io(const RobotInfo *robots, int total_slots,
                                                            const int32_t *slot_robot, const int32_t *slot_node,
                                                            SpringIndex ix, const int64_t *spring_off, Planes pl,
@@ -1642,6 +1647,10 @@ int persist_list(int n, int32_t *blocks, int32_t *variants, int cap) {
 // A robot alone on its CU at 8^3 takes the balanced slot plan with tight rows:
 // 1000 steps of 256 robots 1595 us against 1650 to 1800 with the default, whose
 // 80 registers let two robots share a CU (2790 against 3170 us at 512).
+// Beside other sides it is as fast or faster too (us a step, plan / other default):
+// 30 robots of 4^3 to 12^3 6.90 / 6.94, 256 of them 7.09 / 7.23, 256 of 7^3 to 9^3
+// 2.05 / 2.31, 256 of 5^3 and 8^3 1.99 / 2.06, 256 of 8^3 and 10^3 2.55 / 2.55; above 256
+// robots the order of the launches decides (512 of 4^3 to 12^3 7.3 to 8.4 / 7.5, 1024 9.4 / 9.6).
 constexpr int kAlone8 = 1 + 256 * 3 + 4096 * 4 + 131072 + 262144 + 524288 + 1048576;
 
 int persist_default_block(int n, bool dash, bool vox, bool alone, int *variant) {
